@@ -46,6 +46,8 @@ SIGNATURES = {
     "mclbm_workspace_bytes": (_sz, [_i32, _descp, _i32, _i32]),
     "mclbm_create": (_i32, [_c.POINTER(_ctxp), _i32, _descp, _i32, _i32, _vp, _sz, _vp]),
     "mclbm_destroy": (_i32, [_ctxp]),
+    "mclbm_step_scratch_bytes": (_sz, [_ctxp]),
+    "mclbm_set_step_scratch": (_i32, [_ctxp, _vp, _sz]),
     "mclbm_init": (_i32, [_ctxp, _u64, _dp]),
     "mclbm_get_y": (_i32, [_ctxp, _dp]),
     "mclbm_set_viscosity": (_i32, [_ctxp, _dp]),

@@ -51,6 +51,9 @@ constexpr size_t kHeaderBytes = 4096; // checkpoint header
 constexpr uint64_t kCkptMagic = 0x4d434c424d434b50ull;
 constexpr size_t kFwdHeaderBytes = 256;  // forward checkpoints: the token of the forward that wrote them
 std::atomic<uint64_t> g_fwd_tokens{0};
+constexpr size_t kMaxRuns = 16;       // two-step passes: runs of equal resolution in an ensemble
+// Nodes of a run from which a pass of two steps is the faster way.
+constexpr int64_t kTwoStepNodes = 1 << 20;
 constexpr int kMaxObservablesN = 512;  // the FFT passes are instantiated for n = 8..512
 
 // Leray projection on the 24 perturbation coefficients.
@@ -136,6 +139,18 @@ struct mclbm_ctx {
   int buffer_addr = 1;       // buffer-resource addressing where every sample fits
   int nontemporal = 1;       // non-temporal population loads and stores
   int exact_gamma = 0;       // 1: exact entropic stabiliser (256-thread blocks)
+
+  // two-step passes: the caller's scratch for the state in between, the runs
+  // of consecutive samples of one resolution and stride, and the card's CUs
+  char* scratch = nullptr;
+  size_t scratch_bytes = 0;
+  struct Run {
+    int first, count;
+  };
+  std::vector<Run> runs;
+  int cus = 0;
+  std::map<std::pair<int, int>, int> teams;  // by n and samples of a launch
+  bool single_steps = false;  // launch shapes are being timed: no two-step passes
 
   // launch tables by key
   std::map<std::string, Table> tables;
@@ -278,15 +293,17 @@ mclbm_status reserve_tables(mclbm_ctx* c, int count) {
 }
 
 // Launch table for the samples active at `tick` (stride divides tick), with
-// their AA parities; `all` forces every sample (init, reductions, adjoint).
+// their AA parities; `all` forces every sample (init, reductions, adjoint);
+// `among`, if given, names the samples (by a flag each) it is limited to.
 // The pointer stays valid until the pool is recycled: a caller that holds
 // several tables at once reserves room for them first (reserve_tables).
-mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool parity_zero, const Table** out) {
+mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool parity_zero, const Table** out,
+                       const std::vector<char>* among = nullptr) {
   std::string key = std::to_string(block) + (all ? "A" : "T") + (parity_zero ? "0" : "P") + ":";
   std::vector<Seg> segs;
   int first = 0;
   for (int s = 0; s < c->m; ++s) {
-    const bool active = all || (tick % c->desc[s].stride == 0);
+    const bool active = (all || (tick % c->desc[s].stride == 0)) && (!among || (*among)[s]);
     if (!active) continue;
     Seg g;
     g.sample = s;
@@ -355,10 +372,11 @@ hipEvent_t next_event(mclbm_ctx* c) {
   return c->ev_pool[c->ev_used++];
 }
 
-// One tick: every active sample takes one step; optionally fused reductions.
-mclbm_status run_tick(mclbm_ctx* c, double* record_out) {
+// One tick: every active sample (of those in `among`) takes one step;
+// optionally fused reductions.
+mclbm_status run_tick(mclbm_ctx* c, double* record_out, const std::vector<char>* among = nullptr) {
   const Table* t = nullptr;
-  mclbm_status st = get_table(c, c->tick, false, c->block, false, &t);
+  mclbm_status st = get_table(c, c->tick, false, c->block, false, &t, among);
   if (st != MCLBM_OK) return st;
   if (t->nseg > 0) {
     StepLaunch L = make_launch(c, t, c->pop, nullptr);
@@ -440,7 +458,7 @@ mclbm_status run_graph(mclbm_ctx* c) {
   return MCLBM_OK;
 }
 
-mclbm_status run_plain_ticks(mclbm_ctx* c, int64_t ticks) {
+mclbm_status run_tick_loop(mclbm_ctx* c, int64_t ticks) {
   int64_t left = ticks;
   const int64_t len = graph_length(c);
   while (left > 0) {
@@ -453,6 +471,149 @@ mclbm_status run_plain_ticks(mclbm_ctx* c, int64_t ticks) {
       if (st != MCLBM_OK) return st;
       left -= 1;
     }
+  }
+  return MCLBM_OK;
+}
+
+// ---------------------------------------------------------------- two-step passes
+// Samples are independent, so between records each run of equal resolution
+// may take all its steps at once, in whatever launches suit it. A pass over
+// memory that takes two steps (step2_kernel.h) goes from the state to scratch
+// and back, so it advances a run by four steps at a time, from even parity;
+// the steps before and after are single in-place ones.
+
+size_t state_bytes_of(const mclbm_ctx* c, int s) {
+  return align_up(size_t(c->q) * c->h_samples[s].pstride * c->elem);
+}
+
+// Samples per trip through scratch. Up to 64^3 as many as fit in 2 GiB (more
+// planes per team: fewer rim planes); longer lattices one at a time, whose
+// state is then still in the last-level cache for the way back at 128^3
+// (8 x 128^3: 899 us per two steps one by one, 1050 together) and whose scratch
+// stays small.
+int run_chunk(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
+  if (c->desc[r.first].n > 64) return 1;
+  const size_t per = state_bytes_of(c, r.first);
+  const int most = int(std::max<size_t>(1, (size_t(2) << 30) / per));
+  const int trips = (r.count + most - 1) / most;
+  return (r.count + trips - 1) / trips;
+}
+
+bool two_step_size(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
+  const int n = c->desc[r.first].n;
+  return n <= 512 && int64_t(r.count) * n * n * n >= kTwoStepNodes;
+}
+
+// Bytes of scratch the two-step passes of an ensemble use.
+size_t scratch_bytes_of(const mclbm_ctx* c) {
+  size_t need = 0;
+  for (const auto& r : c->runs)
+    if (two_step_size(c, r)) need = std::max(need, state_bytes_of(c, r.first) * size_t(run_chunk(c, r)));
+  return need;
+}
+
+// Teams of blocks for `count` samples: the number that minimises the rounds of
+// blocks over the CUs times the planes each block marches through, two rim
+// planes per run of planes included.
+int step2_teams(const Step2Tiles& t, int count, int n, int cus) {
+  const int tiles = t.x * t.y, planes = count * n, slots = cus * t.blocks_per_cu;
+  double best = 1e300;
+  int teams = 1;
+  for (int k = 1; k <= planes && int64_t(k) * tiles <= int64_t(8) * slots + tiles; ++k) {
+    const double per = double(planes) / k;
+    const double cost = double((int64_t(k) * tiles + slots - 1) / slots) * (per + 2.0 * (1.0 + per / n));
+    if (cost < 0.98 * best) {
+      best = cost;
+      teams = k;
+    }
+  }
+  return teams;
+}
+
+// Four steps of samples first..first+count-1 at even parity.
+mclbm_status run_two_step_pair(mclbm_ctx* c, int first, int count) {
+  Step2Launch L;
+  L.samples = c->d_samples;
+  L.sample0 = first;
+  L.count = count;
+  L.log2n = c->h_samples[first].log2n;
+  L.tiles = step2_tiles(L.log2n, c->precision);
+  const auto size = std::make_pair(int(c->desc[first].n), count);
+  auto known = c->teams.find(size);
+  if (known == c->teams.end())
+    known = c->teams.emplace(size, step2_teams(L.tiles, count, size.first, c->cus)).first;
+  L.teams = known->second;
+  L.wide = size_t(c->q) * c->h_samples[first].pstride * c->elem >= (size_t(1) << 31);
+  L.flags = c->d_flags;
+  const int64_t away = -int64_t(c->h_samples[first].offset);
+  for (int way = 0; way < 2; ++way) {
+    L.src = way ? c->scratch : c->pop;
+    L.dst = way ? c->pop : c->scratch;
+    L.src_shift = way ? away : 0;
+    L.dst_shift = way ? 0 : away;
+    HIP_TRY(launch_step2(c->q, c->precision, L, c->stream));
+  }
+  for (int s = first; s < first + count; ++s) c->steps[s] += 4;
+  return MCLBM_OK;
+}
+
+// `steps` steps of one run: to even parity, in two-step passes, and the rest.
+mclbm_status run_steps_two(mclbm_ctx* c, const mclbm_ctx::Run& r, int64_t steps) {
+  std::vector<char> among(size_t(c->m), 0);
+  std::fill(among.begin() + r.first, among.begin() + r.first + r.count, 1);
+  const int64_t tick0 = c->tick;
+  auto single = [&]() -> mclbm_status {
+    c->tick = 0;  // a tick on which every sample steps
+    const mclbm_status st = run_tick(c, nullptr, &among);
+    c->tick = tick0;
+    steps -= 1;
+    return st;
+  };
+  mclbm_status st = MCLBM_OK;
+  if (c->steps[r.first] & 1) st = single();
+  const int64_t pairs = steps / 4;
+  const int chunk = run_chunk(c, r);
+  for (int a = r.first; a < r.first + r.count && st == MCLBM_OK; a += chunk)
+    for (int64_t k = 0; k < pairs && st == MCLBM_OK; ++k)
+      st = run_two_step_pair(c, a, std::min(chunk, r.first + r.count - a));
+  steps -= 4 * pairs;
+  while (steps > 0 && st == MCLBM_OK) st = single();
+  return st;
+}
+
+mclbm_status run_plain_ticks(mclbm_ctx* c, int64_t ticks) {
+  // the runs that take two-step passes in this stretch
+  std::vector<char> rest;
+  std::vector<std::pair<const mclbm_ctx::Run*, int64_t>> two;
+  if (c->scratch && !c->exact_gamma && !c->timing && !c->single_steps && c->runs.size() <= kMaxRuns) {
+    for (const auto& r : c->runs) {
+      const int64_t stride = c->desc[r.first].stride;
+      const int64_t steps = (c->tick + ticks + stride - 1) / stride - (c->tick + stride - 1) / stride;
+      bool same = true;
+      for (int s = r.first + 1; s < r.first + r.count; ++s) same = same && !((c->steps[s] ^ c->steps[r.first]) & 1);
+      if (same && two_step_size(c, r) && steps - (c->steps[r.first] & 1) >= 4 &&
+          state_bytes_of(c, r.first) * size_t(run_chunk(c, r)) <= c->scratch_bytes)
+        two.push_back({&r, steps});
+    }
+  }
+  if (two.empty()) return run_tick_loop(c, ticks);
+  int64_t others = c->m;
+  rest.assign(size_t(c->m), 1);
+  for (const auto& t : two) {
+    std::fill(rest.begin() + t.first->first, rest.begin() + t.first->first + t.first->count, 0);
+    others -= t.first->count;
+  }
+  for (const auto& t : two) {
+    const mclbm_status st = run_steps_two(c, *t.first, t.second);
+    if (st != MCLBM_OK) return st;
+  }
+  if (others == 0) {
+    c->tick += ticks;
+    return MCLBM_OK;
+  }
+  for (int64_t k = 0; k < ticks; ++k) {
+    const mclbm_status st = run_tick(c, nullptr, &rest);
+    if (st != MCLBM_OK) return st;
   }
   return MCLBM_OK;
 }
@@ -569,7 +730,32 @@ mclbm_status mclbm_create(mclbm_ctx** out, int32_t m, const mclbm_sample_desc* d
     return fail(MCLBM_ERR_HIP, std::string("context upload: ") + hipGetErrorString(e));
   }
   c->ckpt_header.assign(kHeaderBytes, 0);
+  for (int s = 0; s < m; ++s) {
+    if (s > 0 && desc[s].n == desc[s - 1].n && desc[s].stride == desc[s - 1].stride) c->runs.back().count += 1;
+    else c->runs.push_back({s, 1});
+  }
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+    c->cus = cus;
+  else
+    c->cus = 256;
   *out = c;
+  return MCLBM_OK;
+}
+
+size_t mclbm_step_scratch_bytes(const mclbm_ctx* c) { return c ? scratch_bytes_of(c) : 0; }
+
+mclbm_status mclbm_set_step_scratch(mclbm_ctx* c, void* scratch_dev, size_t bytes) {
+  mclbm_status st = check_ctx(c, false);
+  if (st != MCLBM_OK) return st;
+  if (scratch_dev) {
+    if (reinterpret_cast<uintptr_t>(scratch_dev) % kAlign) return fail(MCLBM_ERR_ARG, "scratch must be 256-byte aligned");
+    if (bytes < scratch_bytes_of(c)) return fail(MCLBM_ERR_OOM, "step scratch too small");
+  }
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  c->scratch = static_cast<char*>(scratch_dev);
+  c->scratch_bytes = scratch_dev ? bytes : 0;
   return MCLBM_OK;
 }
 
@@ -837,7 +1023,8 @@ mclbm_status mclbm_forward_ckpt(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every,
     if (st != MCLBM_OK) return st;
     HIP_TRY(launch_canonical_copy(c->q, c->precision, c->pop, ck + size_t(k) * c->state_bytes, c->d_samples,
                                   table_ptr(c, t), t->nseg, t->total_blocks, c->stream));
-    st = run_plain_ticks(c, std::min<int64_t>(ckpt_every, ticks - k * ckpt_every));
+    // single steps, as the backward sweep takes them when it recomputes
+    st = run_tick_loop(c, std::min<int64_t>(ckpt_every, ticks - k * ckpt_every));
     if (st != MCLBM_OK) return st;
   }
   const uint64_t token = ++g_fwd_tokens;
@@ -1194,6 +1381,7 @@ mclbm_status mclbm_autotune(mclbm_ctx* c, int32_t reps, void* scratch_dev, size_
   const int b0 = c->block, x0 = c->xcd_remap, f0 = c->buffer_addr, n0 = c->nontemporal;
   c->use_graphs = false;
   c->timing = false;
+  c->single_steps = true;
   const int64_t per = 2 * int64_t(c->max_stride) * reps;
   // one trial: warm-up, timed ticks, then the state as it was
   auto trial = [&](float* ms) -> mclbm_status {
@@ -1266,6 +1454,7 @@ mclbm_status mclbm_autotune(mclbm_ctx* c, int32_t reps, void* scratch_dev, size_
   (void)hipEventDestroy(e1);
   c->use_graphs = graphs0;
   c->timing = timing0;
+  c->single_steps = false;
   if (st != MCLBM_OK) {
     // keep the error of the failed trial; put back the shape and the state
     const std::string err = g_last_error;

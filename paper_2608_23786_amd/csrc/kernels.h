@@ -39,6 +39,39 @@ hipError_t launch_step_d3q27_f64(StepKind kind, const StepLaunch& L, hipStream_t
 hipError_t launch_step_d3q19_f32(StepKind kind, const StepLaunch& L, hipStream_t s);
 hipError_t launch_step_d3q19_f64(StepKind kind, const StepLaunch& L, hipStream_t s);
 
+// Two steps in one pass over memory (step2_kernel.h) of `count` samples
+// sample0.. of one resolution, from a state in the natural layout to another
+// one in a different buffer; closed-form stabiliser.
+struct Step2Tiles {
+  int32_t x, y;              // tiles per plane
+  int32_t blocks_per_cu;     // blocks of the tile that fit one CU
+};
+// Row ends and rows per tile: a tile of R rows with a rim covers R - 2.
+inline Step2Tiles step2_tiles(int log2n, int precision) {
+  const int n = 1 << log2n;
+  const bool f32 = precision != 0;
+  if (log2n <= 4) return {1, 1, (f32 ? 4 : 2) * (log2n == 3 ? 4 : 1)};
+  if (log2n == 5) return f32 ? Step2Tiles{1, 1, 1} : Step2Tiles{1, (n + 13) / 14, 1};
+  if (log2n == 6) return {1, f32 ? (n + 13) / 14 : (n + 5) / 6, 1};
+  return {n / 64, f32 ? (n + 12) / 13 : (n + 4) / 5, 1};
+}
+struct Step2Launch {
+  const void* src;
+  void* dst;
+  int64_t src_shift, dst_shift;  // elements added to DevSample::offset for the sample's place in src, dst
+  const DevSample* samples;
+  int32_t sample0, count, log2n;
+  Step2Tiles tiles;
+  int32_t teams;             // teams of tiles.x * tiles.y blocks, at most count * n
+  int32_t wide;              // a sample's populations span 2 GiB or more
+  int32_t* flags;
+};
+hipError_t launch_step2(int q, int precision, const Step2Launch& L, hipStream_t s);
+hipError_t launch_step2_d3q27_f32(const Step2Launch& L, hipStream_t s);
+hipError_t launch_step2_d3q27_f64(const Step2Launch& L, hipStream_t s);
+hipError_t launch_step2_d3q19_f32(const Step2Launch& L, hipStream_t s);
+hipError_t launch_step2_d3q19_f64(const Step2Launch& L, hipStream_t s);
+
 // Records from block partials: one block per segment, writes out[sample*kRecord + k].
 hipError_t launch_record_finalize(const double* partials, const Seg* segs, int32_t nseg, const DevSample* samples,
                                   double* out, hipStream_t s);

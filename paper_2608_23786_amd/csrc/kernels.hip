@@ -617,6 +617,12 @@ hipError_t launch_step(int q, int precision, StepKind kind, const StepLaunch& L,
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_step2(int q, int precision, const Step2Launch& L, hipStream_t s) {
+  if (q == 27) return precision == 0 ? launch_step2_d3q27_f64(L, s) : launch_step2_d3q27_f32(L, s);
+  if (q == 19) return precision == 0 ? launch_step2_d3q19_f64(L, s) : launch_step2_d3q19_f32(L, s);
+  return hipErrorInvalidValue;
+}
+
 hipError_t launch_record_finalize(const double* partials, const Seg* segs, int32_t nseg, const DevSample* samples,
                                   double* out, hipStream_t s) {
   hipLaunchKernelGGL(record_finalize_kernel, dim3(nseg), dim3(256), 0, s, partials, segs, samples, out);

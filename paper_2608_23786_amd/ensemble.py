@@ -74,6 +74,8 @@ class Ensemble:
         self._ctx = ctypes.c_void_p()
         check(L.mclbm_create(ctypes.byref(self._ctx), self.m, self._desc, PRECISIONS[precision], self.q,
                              ctypes.c_void_p(self._ws_ptr), nbytes, ctypes.c_void_p(self.stream.cuda_stream)))
+        self._scratch = None
+        self.two_step(True)
 
     def __del__(self):
         ctx = getattr(self, "_ctx", None)
@@ -111,6 +113,32 @@ class Ensemble:
         for t in outputs:
             if t is not None:
                 t.record_stream(cur)
+
+    def two_step(self, enable: bool) -> bool:
+        """Give the library the scratch buffer with which steps between records
+        take two steps per pass over memory (same results, bitwise), or take
+        it back. Ensembles too small to gain need none, and where the buffer
+        does not fit, or one of more than 4 GiB would take over a quarter of the
+        free device memory, the ensemble keeps single steps. Returns whether a
+        buffer is set."""
+        if enable and self._scratch is not None:
+            return True
+        nb = int(lib().mclbm_step_scratch_bytes(self._ctx)) if enable else 0
+        if nb > 4 << 30 and nb > torch.cuda.mem_get_info(self.device)[0] // 4:
+            nb = 0
+        scratch = None
+        if nb:
+            try:
+                scratch = torch.empty(nb + 256, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                pass
+        if scratch is not None:
+            base = (scratch.data_ptr() + 255) // 256 * 256
+            check(lib().mclbm_set_step_scratch(self._ctx, ctypes.c_void_p(base), nb))
+        elif self._scratch is not None:
+            check(lib().mclbm_set_step_scratch(self._ctx, None, 0))
+        self._scratch = scratch
+        return scratch is not None
 
     # ------------------------------------------------------------ lifecycle
     def init(self, seed: int = 0, y: Optional[torch.Tensor] = None):
