@@ -479,8 +479,8 @@ mclbm_status run_tick_loop(mclbm_ctx* c, int64_t ticks) {
 // Samples are independent, so between records each run of equal resolution
 // may take all its steps at once, in whatever launches suit it. A pass over
 // memory that takes two steps (step2_kernel.h) goes from the state to scratch
-// and back, so it advances a run by four steps at a time, from even parity;
-// the steps before and after are single in-place ones.
+// and back, so it advances a run by four steps at a time, from the parity its
+// layout has; the steps before and after are single in-place ones.
 
 size_t state_bytes_of(const mclbm_ctx* c, int s) {
   return align_up(size_t(c->q) * c->h_samples[s].pstride * c->elem);
@@ -502,6 +502,11 @@ int run_chunk(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
 bool two_step_size(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   const int n = c->desc[r.first].n;
   return n <= 512 && int64_t(r.count) * n * n * n >= kTwoStepNodes;
+}
+
+// Whether a run is one step from the parity its passes start from.
+bool parity_off(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
+  return int(c->steps[r.first] & 1) != step2_parity(c->h_samples[r.first].log2n);
 }
 
 // Bytes of scratch the two-step passes of an ensemble use.
@@ -530,7 +535,7 @@ int step2_teams(const Step2Tiles& t, int count, int n, int cus) {
   return teams;
 }
 
-// Four steps of samples first..first+count-1 at even parity.
+// Four steps of samples first..first+count-1 at the parity of the passes.
 mclbm_status run_two_step_pair(mclbm_ctx* c, int first, int count) {
   Step2Launch L;
   L.samples = c->d_samples;
@@ -557,7 +562,7 @@ mclbm_status run_two_step_pair(mclbm_ctx* c, int first, int count) {
   return MCLBM_OK;
 }
 
-// `steps` steps of one run: to even parity, in two-step passes, and the rest.
+// `steps` steps of one run: to the parity of the passes, in passes, and the rest.
 mclbm_status run_steps_two(mclbm_ctx* c, const mclbm_ctx::Run& r, int64_t steps) {
   std::vector<char> among(size_t(c->m), 0);
   std::fill(among.begin() + r.first, among.begin() + r.first + r.count, 1);
@@ -570,7 +575,7 @@ mclbm_status run_steps_two(mclbm_ctx* c, const mclbm_ctx::Run& r, int64_t steps)
     return st;
   };
   mclbm_status st = MCLBM_OK;
-  if (c->steps[r.first] & 1) st = single();
+  if (parity_off(c, r)) st = single();
   const int64_t pairs = steps / 4;
   const int chunk = run_chunk(c, r);
   for (int a = r.first; a < r.first + r.count && st == MCLBM_OK; a += chunk)
@@ -591,7 +596,7 @@ mclbm_status run_plain_ticks(mclbm_ctx* c, int64_t ticks) {
       const int64_t steps = (c->tick + ticks + stride - 1) / stride - (c->tick + stride - 1) / stride;
       bool same = true;
       for (int s = r.first + 1; s < r.first + r.count; ++s) same = same && !((c->steps[s] ^ c->steps[r.first]) & 1);
-      if (same && two_step_size(c, r) && steps - (c->steps[r.first] & 1) >= 4 &&
+      if (same && two_step_size(c, r) && steps - parity_off(c, r) >= 4 &&
           state_bytes_of(c, r.first) * size_t(run_chunk(c, r)) <= c->scratch_bytes)
         two.push_back({&r, steps});
     }

@@ -40,8 +40,9 @@ hipError_t launch_step_d3q19_f32(StepKind kind, const StepLaunch& L, hipStream_t
 hipError_t launch_step_d3q19_f64(StepKind kind, const StepLaunch& L, hipStream_t s);
 
 // Two steps in one pass over memory (step2_kernel.h) of `count` samples
-// sample0.. of one resolution, from a state in the natural layout to another
-// one in a different buffer; closed-form stabiliser.
+// sample0.. of one resolution, from a state in the layout of parity
+// step2_parity() to another one in a different buffer; closed-form stabiliser.
+inline int step2_parity(int log2n) { return log2n > 6; }
 struct Step2Tiles {
   int32_t x, y;              // tiles per plane
   int32_t blocks_per_cu;     // blocks of the tile that fit one CU

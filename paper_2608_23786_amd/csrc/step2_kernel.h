@@ -3,10 +3,17 @@
 // One step moves 2 q values per node through HBM and runs at the copy rate of
 // the card, so the only way to go faster is to move less: this kernel reads
 // the populations of a state once, takes two steps, and writes them once.
-// Source and destination are different buffers, both in the natural layout
-// (slot i of a node holds population i before its collision: the layout of
-// the in-place scheme before an even step), so a pair of launches, there and
-// back, advances the in-place state by four steps.
+// Source and destination are different buffers in the same layout; a pair of
+// launches, there and back, advances the in-place state by four steps. Either
+// layout of the in-place scheme serves. After an even number of steps slot i of
+// a node holds population i before its collision: the loads are to the node's own
+// place and the stores stream. After an odd number slot -i holds population i
+// after its collision: the loads stream (population i of node x from x - c_i) and
+// the stores are to the node's own place. Rows that lie whole in a tile stay in
+// whole lines either way and take the even layout (64 x 64^3: 794 us a pass
+// against 839); 64-node tiles of longer rows take the odd one, since stores off
+// their lines by one node write them in parts (256^3: 1.12 x the bytes, 1028 us
+// against 891; 8 x 128^3: 1050 against 887).
 //
 // A block owns a tile of nodes in the x-y plane and marches along z. Per plane
 // it loads the 27 populations of its nodes, takes the first collision, and
@@ -16,8 +23,7 @@
 // values that change row (c_y != 0) wait in LDS, those with c_z = -1, 0, +1 for
 // the second collision of the same, the next and the next but one iteration,
 // so 1, 2 and 3 planes of them are held: (6 + 12 + 18) values per node for
-// D3Q27, 147 KB of the CU's 160 KB for 1024 nodes. The second collision's
-// results are stored at the neighbours they stream to.
+// D3Q27, 147 KB of the CU's 160 KB for 1024 nodes.
 //
 // The first collision is taken in the tile's rim as well (redundantly in the
 // neighbouring tiles): one row on each side in y unless the tile spans the
@@ -148,6 +154,7 @@ __global__ void __launch_bounds__((R + SIDE) * LX) kbc_step2_kernel(Step2Args<T>
   constexpr int STRIDE = LX + 2 * SIDE, NODES = R * STRIDE;      // LDS elements per row and per plane of values
   constexpr bool UNIFORM_ROW = LX == 64;                         // a wave lies in one row (or in the rim columns)
   constexpr int RPW = 64 / LX;                                   // rows per wave
+  constexpr bool PULL = SIDE;                                    // the layout of odd parity
   constexpr uint32_t S = uint32_t(sizeof(T));
   constexpr int NM = row_count<QN>(-1), N0 = row_count<QN>(0), NP = row_count<QN>(1);
   __shared__ T lds[lds_planes<QN>() * NODES];
@@ -229,13 +236,28 @@ __global__ void __launch_bounds__((R + SIDE) * LX) kbc_step2_kernel(Step2Args<T>
     bool bad = false;
 
     T g[Q];
+    // byte offsets of the nodes around (x, y, z) against (SIGN -1) or along (+1)
+    // the velocities, by c + 1 per axis
+    auto around = [&](auto sign, int col, int row, int z, uint32_t (&xb)[3], uint32_t (&yb)[3], uint32_t (&zb)[3]) {
+      constexpr int SIGN = decltype(sign)::value;
+      const uint32_t x = uint32_t(x0 + col - SIDE), y = uint32_t(y0 + row - HY);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const uint32_t d = uint32_t(SIGN * (c - 1));
+        xb[c] = ((x + d) & msk) * S;
+        yb[c] = (((y + d) & msk) << l) * S;
+        zb[c] = ((uint32_t(z) + d) & msk) * zbytes;
+      }
+    };
     auto load_plane = [&](int zz) {
       int col, row;
       thread(col, row);
-      const uint32_t x = uint32_t(x0 + col - SIDE) & msk, y = uint32_t(y0 + row - HY) & msk;
-      const uint32_t xy = ((y << l) + x) * S, zb = (uint32_t(zz) & msk) * zbytes;
+      uint32_t xb[3], yb[3], zb[3];
+      around(std::integral_constant<int, -1>{}, col, row, zz, xb, yb, zb);
       src.for_planes([&](__amdgpu_buffer_rsrc_t rs, uint32_t plane, auto ic) {
-        g[decltype(ic)::value] = slab_load<T>(rs, xy, plane + zb);
+        constexpr int i = PULL ? opposite(decltype(ic)::value) : decltype(ic)::value;
+        if constexpr (PULL) g[i] = slab_load<T>(rs, xb[cx(i) + 1] + yb[cy(i) + 1], plane + zb[cz(i) + 1]);
+        else g[i] = slab_load<T>(rs, xb[1] + yb[1], plane + zb[1]);
       });
     };
 
@@ -370,15 +392,14 @@ __global__ void __launch_bounds__((R + SIDE) * LX) kbc_step2_kernel(Step2Args<T>
         row_thread(col, row);
         const bool out = !(HY && RPW > 1) || (row >= 1 && row <= ny);
         bad = bad || (out && res.bad);
-        const uint32_t x = uint32_t(x0 + col - SIDE), y = uint32_t(y0 + row - HY);
-        const uint32_t xb[3] = {((x - 1u) & msk) * S, (x & msk) * S, ((x + 1u) & msk) * S};
-        const uint32_t yb[3] = {(((y - 1u) & msk) << l) * S, ((y & msk) << l) * S, (((y + 1u) & msk) << l) * S};
-        const uint32_t zb[3] = {(uint32_t(zz - 2) & msk) * zbytes, (uint32_t(zz - 1) & msk) * zbytes,
-                                (uint32_t(zz) & msk) * zbytes};
         if (out) {
+          uint32_t xb[3], yb[3], zb[3];
+          around(std::integral_constant<int, 1>{}, col, row, zz - 1, xb, yb, zb);
           dst.for_planes([&](__amdgpu_buffer_rsrc_t rs, uint32_t plane, auto ic) {
             constexpr int i = decltype(ic)::value;
-            if constexpr (UNIFORM_ROW)
+            if constexpr (PULL)
+              slab_store<T>(rs, xb[1] + yb[1], plane + zb[1], f[opposite(i)]);
+            else if constexpr (UNIFORM_ROW)
               slab_store<T>(rs, xb[cx(i) + 1], plane + zb[cz(i) + 1] + yb[cy(i) + 1], f[i]);
             else
               slab_store<T>(rs, yb[cy(i) + 1] + xb[cx(i) + 1], plane + zb[cz(i) + 1], f[i]);

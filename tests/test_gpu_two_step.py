@@ -52,18 +52,18 @@ def _same_records(ra, rb, steps):
 def test_states_equal_single_steps(n, m, precision, lattice):
     a, b = (_ensemble(n, m, precision, lattice, two) for two in (True, False))
     last = sorted({0, m // 2, m - 1})
-    for ticks in (1, 5, 4, 7):      # odd start, remainders 0 and 3, an odd lead step
+    for ticks in (1, 5, 5, 10):     # starts at odd and even parity, with and without remainder, one and two trips
         a.step(ticks)
         b.step(ticks)
         _same_state(a, b, last)
-    assert a.steps(m - 1) == b.steps(m - 1) == 17 and a.ticks == b.ticks == 17
+    assert a.steps(m - 1) == b.steps(m - 1) == 21 and a.ticks == b.ticks == 21
 
 
 def test_512_takes_64_bit_addresses():
     states = []
     for two in (True, False):
         a = _ensemble(512, 1, "f32s", 27, two)
-        a.step(4)
+        a.step(5)
         g = torch.Generator(device="cpu").manual_seed(3)
         cells = torch.cat([torch.randint(0, 512 ** 3, (4096,), generator=g), torch.tensor([0, 512 ** 3 - 1])])
         states.append((a.get_cells(0, cells), a.reduce()))
@@ -71,8 +71,8 @@ def test_512_takes_64_bit_addresses():
         torch.cuda.empty_cache()
     (fa, ra), (fb, rb) = states
     scale = float((fb - fb.mean(dim=0)).abs().max())
-    assert float((fa - fb).abs().max()) <= FP32_STEP * 4 * scale
-    _same_records(ra, rb, 4)
+    assert float((fa - fb).abs().max()) <= FP32_STEP * 5 * scale
+    _same_records(ra, rb, 5)
 
 
 def test_records_between_passes():
@@ -113,7 +113,7 @@ def test_instability_is_flagged():
     a = _ensemble(64, 6, "f32s", 27, True)
     a.step(2)
     a.poison(4, 12345, 7)
-    a.step(4)
+    a.step(5)
     assert a.check() == 4
 
 
