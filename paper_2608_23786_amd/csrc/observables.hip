@@ -837,8 +837,99 @@ __global__ void __launch_bounds__(64) point_values_kernel(const T* pop, const De
   o[2 * q3 + j] = jzs / rho;
 }
 
-// One block per (component, node): sort the m values of both ensembles and
-// average |a_(i) - b_(i)| (bitonic sort in LDS, m <= 4096).
+__device__ __forceinline__ double flip_sign(double v, uint32_t sign) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, u ^ (uint64_t(sign) << 32));
+}
+
+// Sorting a column of 64 E values in the registers of one wave (bitonic):
+// position i of the sorted order is element i % E of lane i / E. Steps of the
+// network whose partner lies E or more positions away exchange between lanes,
+// the others inside a lane, both without barriers. Merges that run downwards in
+// a lane run upwards on the negated values, so that the direction costs one
+// sign flip per value and merge instead of selects in every step.
+template <int E>
+__device__ __forceinline__ void wave_sort(double (&v)[E], int lane) {
+  static_for<1, log2_of<64 * E>() + 1>([&](auto kc) {
+    constexpr int k = 1 << decltype(kc)::value;
+    const uint32_t sign = k >= E && ((lane * E) & k) != 0 ? 0x80000000u : 0u;
+    if constexpr (k >= E) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = flip_sign(v[e], sign);
+    }
+    static_for<0, decltype(kc)::value>([&](auto jc) {
+      constexpr int j = k >> (decltype(jc)::value + 1);
+      if constexpr (j >= E) {
+        const bool low = ((lane * E) & j) == 0;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const double o = __shfl_xor(v[e], j / E, 64);
+          const double lo = fmin(v[e], o), hi = fmax(v[e], o);
+          v[e] = low ? lo : hi;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          if ((e & j) == 0) {
+            const bool up = k >= E || (e & k) == 0;
+            const double lo = fmin(v[e], v[e | j]), hi = fmax(v[e], v[e | j]);
+            v[e] = up ? lo : hi;
+            v[e | j] = up ? hi : lo;
+          }
+        }
+      }
+    });
+    if constexpr (k >= E) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = flip_sign(v[e], sign);
+    }
+  });
+}
+
+// Columns of one block of w1_wave_kernel, one wave each: neighbouring columns
+// share the 64-byte segments that the rows are read in.
+constexpr int kW1Columns = 4;
+
+// One wave per (component, node), for m <= 64 E: sort the m values of both
+// ensembles in registers and average |a_(i) - b_(i)|. The values come through
+// LDS so that the block reads each row's neighbouring columns together. A NaN
+// (which minima drop) makes the column NaN. Bound by the network's
+// instructions: 1000 values of 1536 columns 163 us in LDS with a barrier per
+// step, one block per column, against 52.
+template <int E>
+__global__ void __launch_bounds__(64 * kW1Columns)
+    w1_wave_kernel(const double* a, const double* b, int m, int q3, double* col) {
+  __shared__ double tile[kW1Columns][64 + 1];
+  const int c0 = blockIdx.x * kW1Columns, columns = 3 * q3;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tr = threadIdx.x / kW1Columns, tc = threadIdx.x % kW1Columns;
+  double v[2][E];
+  bool nan = false;
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const double* x = side ? b : a;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int row = 64 * e + tr;
+      tile[tc][tr] = row < m && c0 + tc < columns ? x[size_t(row) * columns + c0 + tc] : 1.0e308;
+      __syncthreads();
+      v[side][e] = tile[w][lane];
+      nan = nan || v[side][e] != v[side][e];
+      __syncthreads();
+    }
+    wave_sort<E>(v[side], lane);
+  }
+  double acc = 0.0;
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+    if (lane * E + e < m) acc += fabs(v[0][e] - v[1][e]);
+  acc = wave_sum(acc);
+  if (__any(nan)) acc = __builtin_nan("");
+  if (lane == 0 && c0 + w < columns) col[c0 + w] = acc / m;
+}
+
+// The same with one block per column for 1024 < m <= 4096, more values than a
+// wave's registers hold in a network of bounded code size: bitonic sort in LDS.
 __global__ void __launch_bounds__(256) w1_column_kernel(const double* a, const double* b, int m, int q3, int p2,
                                                         double* col) {
   __shared__ double sa[4096], sb[4096];
@@ -1150,7 +1241,13 @@ hipError_t launch_w1(const double* a, const double* b, int m, int q, double* col
   const int q3 = q * q * q;
   int p2 = 1;
   while (p2 < m) p2 <<= 1;
-  hipLaunchKernelGGL(w1_column_kernel, dim3(unsigned(3 * q3)), dim3(256), 0, s, a, b, m, q3, p2, col);
+  const dim3 waves(unsigned((3 * q3 + kW1Columns - 1) / kW1Columns)), block(64 * kW1Columns);
+  if (p2 <= 64) hipLaunchKernelGGL(w1_wave_kernel<1>, waves, block, 0, s, a, b, m, q3, col);
+  else if (p2 == 128) hipLaunchKernelGGL(w1_wave_kernel<2>, waves, block, 0, s, a, b, m, q3, col);
+  else if (p2 == 256) hipLaunchKernelGGL(w1_wave_kernel<4>, waves, block, 0, s, a, b, m, q3, col);
+  else if (p2 == 512) hipLaunchKernelGGL(w1_wave_kernel<8>, waves, block, 0, s, a, b, m, q3, col);
+  else if (p2 == 1024) hipLaunchKernelGGL(w1_wave_kernel<16>, waves, block, 0, s, a, b, m, q3, col);
+  else hipLaunchKernelGGL(w1_column_kernel, dim3(unsigned(3 * q3)), dim3(256), 0, s, a, b, m, q3, p2, col);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(w1_reduce_kernel, dim3(3), dim3(256), 0, s, col, q3, out);
