@@ -89,6 +89,7 @@ struct Table {
   size_t offset = 0;         // byte offset of the Seg array in the table pool
   int nseg = 0;
   int total_blocks = 0;
+  int most_blocks = 0;       // of one segment
   std::vector<Seg> host;     // persistent host copy (source of the upload)
 };
 
@@ -327,6 +328,7 @@ mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool par
   t.offset = c->table_next;
   t.nseg = int(segs.size());
   t.total_blocks = first;
+  for (const Seg& g : segs) t.most_blocks = std::max(t.most_blocks, int(g.nblocks));
   t.host = segs;
   c->table_next += slot;
   if (!segs.empty()) {
@@ -390,7 +392,7 @@ mclbm_status run_tick(mclbm_ctx* c, double* record_out, const std::vector<char>*
     HIP_TRY(launch_step(c->q, c->precision, record_out ? kStepRecord : kStep, L, c->stream));
     if (c->timing) HIP_TRY(hipEventRecord(e1, c->stream));
     if (record_out)
-      HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, c->d_samples, record_out, c->stream));
+      HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, record_out, c->stream));
     for (const Seg& g : t->host) c->steps[g.sample] += 1;
   }
   c->tick += 1;
@@ -807,7 +809,7 @@ mclbm_status mclbm_init(mclbm_ctx* c, uint64_t seed, const double* y_host) {
   st = get_table(c, 0, true, kAuxBlock, true, &t);
   if (st != MCLBM_OK) return st;
   c->generation += 1;
-  HIP_TRY(launch_init(c->q, c->precision, c->pop, c->d_samples, table_ptr(c, t), t->nseg, t->total_blocks, c->d_ycoef,
+  HIP_TRY(launch_init(c->q, c->precision, c->pop, c->d_samples, table_ptr(c, t), t->nseg, t->total_blocks, t->most_blocks, c->d_ycoef,
                       c->stream));
   c->initialized = true;
   return MCLBM_OK;
@@ -886,7 +888,7 @@ mclbm_status mclbm_reduce(mclbm_ctx* c, double* red_dev) {
   if (st != MCLBM_OK) return st;
   StepLaunch L = make_launch(c, t, c->pop, nullptr);
   HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
-  HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, c->d_samples, red_dev, c->stream));
+  HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, red_dev, c->stream));
   return check_flags(c, nullptr);
 }
 
@@ -1074,7 +1076,7 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
     if (st != MCLBM_OK) return st;
     StepLaunch L = make_launch(c, t, c->pop, nullptr);
     HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
-    HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, c->d_samples, records, c->stream));
+    HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, records, c->stream));
     HIP_TRY(launch_extract(records, c->m, 4, ke_dev, c->stream));
   }
 
@@ -1113,8 +1115,8 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
     }
   }
   HIP_TRY(launch_init_adjoint(c->q, c->precision, lam[cur], c->d_samples, table_ptr(c, nat), nat->nseg, nat->total_blocks,
-                              c->d_ycoef, partials, c->stream));
-  HIP_TRY(launch_init_adjoint_finalize(partials, table_ptr(c, nat), nat->nseg, c->d_samples, c->d_pmat, dJdY_dev,
+                              nat->most_blocks, c->d_ycoef, partials, c->stream));
+  HIP_TRY(launch_init_adjoint_finalize(partials, table_ptr(c, nat), nat->nseg, nat->total_blocks, c->d_samples, c->d_pmat, dJdY_dev,
                                        c->stream));
   return MCLBM_OK;
 }

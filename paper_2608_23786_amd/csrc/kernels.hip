@@ -1,24 +1,57 @@
 // HIP kernels (gfx950) of the library other than collide-and-stream:
 // reductions, initial data, read-out and state access, the adjoint sweep and
 // the plain copy kernel used as the bandwidth reference.
+#include <algorithm>
+
 #include "lbm_device.h"
 
 namespace mclbm {
 namespace {
 
-__global__ void __launch_bounds__(256)
-    record_finalize_kernel(const double* partials, const Seg* segs, const DevSample* samples, double* out) {
-  const Seg sg = segs[blockIdx.x];
+constexpr int kMaxGridY = 65535;
+
+// Records from the block partials, in two stages where a sample has more than
+// kRecordChunk blocks: each block of the first adds up kRecordChunk rows in place,
+// into the first of them (which no other block touches), and the second stage
+// takes one block per segment over those rows. One block over the 65536 rows of
+// a 256^3 sample took 96 us; the two stages take 9.
+constexpr int kRecordChunk = 1024;
+
+__device__ __forceinline__ void add_record_rows(const double* rows, int count, size_t stride, double (&res)[kRecord]) {
   double v[kRecord] = {0, 0, 0, 0, 0, 0, 1e300, -1e300};
-  for (int k = threadIdx.x; k < sg.nblocks; k += 256) {
-    const double* p = partials + size_t(sg.first_block + k) * kRecord;
+  for (int k = threadIdx.x; k < count; k += 256) {
+    const double* p = rows + size_t(k) * stride * kRecord;
 #pragma unroll
     for (int q = 0; q < 6; ++q) v[q] += p[q];
     v[6] = fmin(v[6], p[6]);
     v[7] = fmax(v[7], p[7]);
   }
-  double res[kRecord];
   block_record<256>(v, res);
+}
+
+__global__ void __launch_bounds__(256) record_chunk_kernel(double* partials, const Seg* segs, int nseg) {
+  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
+    const Seg sg = segs[k];
+    const int first = blockIdx.x * kRecordChunk, left = sg.nblocks - first;
+    if (sg.nblocks <= kRecordChunk || left <= 0) continue;
+    double* rows = partials + size_t(sg.first_block + first) * kRecord;
+    double res[kRecord];
+    add_record_rows(rows, left < kRecordChunk ? left : kRecordChunk, 1, res);
+    if (threadIdx.x == 0) {  // after the barrier of the reduction: every row is read
+#pragma unroll
+      for (int q = 0; q < kRecord; ++q) rows[q] = res[q];
+    }
+    __syncthreads();  // the reduction's LDS is free again
+  }
+}
+
+__global__ void __launch_bounds__(256)
+    record_finalize_kernel(const double* partials, const Seg* segs, const DevSample* samples, double* out) {
+  const Seg sg = segs[blockIdx.x];
+  const bool chunked = sg.nblocks > kRecordChunk;
+  double res[kRecord];
+  add_record_rows(partials + size_t(sg.first_block) * kRecord,
+                  chunked ? (sg.nblocks + kRecordChunk - 1) / kRecordChunk : sg.nblocks, chunked ? kRecordChunk : 1, res);
   if (threadIdx.x == 0) {
     const DevSample& sp = samples[sg.sample];
     const double ncell = double(uint64_t(1) << (3 * sp.log2n));
@@ -36,55 +69,65 @@ __global__ void __launch_bounds__(256)
 
 // ---------------------------------------------------------------- initial data
 // u0(x) = u0 [TGV(x) + amp * s(x)] with s from the (projected) coefficients yc[24].
-struct Basis {
-  double a[3][2];  // a[axis][0] = sin(2 x_axis), a[axis][1] = cos(2 x_axis)
-};
+// The kernels of the initial data take groups of 256 consecutive nodes, `per` of
+// them per block, and look sin and cos up in a table of the block: 11 of them
+// per node in double cost more than the rest of the node's work (init of
+// 1000 x 32^3 D3Q19 in float 613 -> 432 us).
+constexpr int kMaxN = 1024;
 
-__device__ __forceinline__ void initial_velocity(uint32_t cell, int l, double u0, double amp, const double* yc,
-                                                 double (&u)[3], Basis& bs) {
-  const uint32_t msk = (1u << l) - 1u;
-  const double n = double(1u << l);
-  const uint32_t x = cell & msk, y = (cell >> l) & msk, z = cell >> (2 * l);
-  // x_k = 2 pi k / n: sin(x_k) = sinpi(2k/n), sin(2 x_k) = sinpi(4k/n)
-  const double s1x = sinpi(2.0 * x / n), c1x = cospi(2.0 * x / n);
-  const double s1y = sinpi(2.0 * y / n), c1y = cospi(2.0 * y / n);
-  const double c1z = cospi(2.0 * z / n);
-  bs.a[0][0] = sinpi(4.0 * x / n);
-  bs.a[0][1] = cospi(4.0 * x / n);
-  bs.a[1][0] = sinpi(4.0 * y / n);
-  bs.a[1][1] = cospi(4.0 * y / n);
-  bs.a[2][0] = sinpi(4.0 * z / n);
-  bs.a[2][1] = cospi(4.0 * z / n);
+// sc[k] = (sin, cos) of 2 pi k / n; sin(2 x_k) is the entry of 2 k
+__device__ __forceinline__ void make_axis_table(double2* sc, int n) {
+  for (int k = threadIdx.x; k < n; k += 256) sc[k] = make_double2(sinpi(2.0 * k / n), cospi(2.0 * k / n));
+}
+
+__device__ __forceinline__ void initial_velocity(const double2& x1, const double2& x2, const double2& y1,
+                                                 const double2& y2, const double2& z1, const double2& z2, double u0,
+                                                 double amp, const double* yc, double (&u)[3]) {
+  const double a[3][2] = {{x2.x, x2.y}, {y2.x, y2.y}, {z2.x, z2.y}};  // sin(2 x_axis), cos(2 x_axis)
   double s[3] = {0.0, 0.0, 0.0};
   for (int al = 0; al < 3; ++al)
     for (int i = 0; i < 2; ++i)
       for (int j = 0; j < 2; ++j)
-        for (int k = 0; k < 2; ++k)
-          s[al] += yc[8 * al + 4 * i + 2 * j + k] * bs.a[0][i] * bs.a[1][j] * bs.a[2][k];
-  u[0] = u0 * (s1x * c1y * c1z + amp * 0.125 * s[0]);
-  u[1] = u0 * (-c1x * s1y * c1z + amp * 0.125 * s[1]);
+        for (int k = 0; k < 2; ++k) s[al] += yc[8 * al + 4 * i + 2 * j + k] * a[0][i] * a[1][j] * a[2][k];
+  u[0] = u0 * (x1.x * y1.y * z1.y + amp * 0.125 * s[0]);
+  u[1] = u0 * (-x1.y * y1.x * z1.y + amp * 0.125 * s[1]);
   u[2] = u0 * (amp * 0.125 * s[2]);
 }
 
 template <int QN, typename T>
 __global__ void __launch_bounds__(256)
-    init_kernel(T* pop, const DevSample* samples, const Seg* segs, int nseg, const double* ycoef) {
-  const int b = blockIdx.x;
-  const Seg sg = segs[find_segment(segs, nseg, b)];
-  const DevSample& sp = samples[sg.sample];
-  const int l = sp.log2n;
-  const uint32_t cell = uint32_t(b - sg.first_block) * 256u + threadIdx.x;
-  double u[3];
-  Basis bs;
-  initial_velocity(cell, l, sp.u0, sp.amp, ycoef + size_t(sg.sample) * 24, u, bs);
-  const double usq15 = 1.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-  T* base = pop + sp.offset;
-  for_vel<QN>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    const double cu = double(cx(i)) * u[0] + double(cy(i)) * u[1] + double(cz(i)) * u[2];
-    const double gi = weight<QN>(i) * (3.0 * cu + 4.5 * cu * cu - usq15);
-    st(base + size_t(plane_of<QN>(i)) * sp.pstride, cell, T(gi));
-  });
+    init_kernel(T* __restrict__ pop, const DevSample* __restrict__ samples, const Seg* __restrict__ segs, int nseg, int per,
+                const double* __restrict__ ycoef) {
+  __shared__ double2 sc[kMaxN];
+  int table_n = 0;
+  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
+    const Seg sg = segs[k];
+    const int first = blockIdx.x * per, last = first + per < sg.nblocks ? first + per : sg.nblocks;
+    if (first >= last) continue;
+    const DevSample& sp = samples[sg.sample];
+    const int l = sp.log2n, n = 1 << l, msk = n - 1;
+    if (n != table_n) {
+      __syncthreads();
+      make_axis_table(sc, n);
+      __syncthreads();
+      table_n = n;
+    }
+    const double* yc = ycoef + size_t(sg.sample) * 24;
+    T* base = pop + sp.offset;
+    for (int b = first; b < last; ++b) {
+      const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
+      const int x = int(cell) & msk, y = int(cell >> l) & msk, z = int(cell >> (2 * l));
+      double u[3];
+      initial_velocity(sc[x], sc[(2 * x) & msk], sc[y], sc[(2 * y) & msk], sc[z], sc[(2 * z) & msk], sp.u0, sp.amp, yc, u);
+      const double usq15 = 1.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+      for_vel<QN>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const double cu = double(cx(i)) * u[0] + double(cy(i)) * u[1] + double(cz(i)) * u[2];
+        const double gi = weight<QN>(i) * (3.0 * cu + 4.5 * cu * cu - usq15);
+        st(base + size_t(plane_of<QN>(i)) * sp.pstride, cell, T(gi));
+      });
+    }
+  }
 }
 
 // ---------------------------------------------------------------- read-out and state access
@@ -471,68 +514,136 @@ __global__ void __launch_bounds__(256) adjoint_step_kernel(const T* state, const
 
 // dJ/du0(x) = sum_i lambda_0,i w_i [3 c_i + 9 (c_i.u0) c_i - 3 u0]; projected on the
 // 24 basis products with factor amp * u0 / 8 (before the projection matrix).
+// A block takes `per` groups of 256 nodes. Its sums over the nodes factor per
+// axis, sum_x a_i(x) sum_(y,z) a_j(y) a_k(z) ubar(x, y, z): groups that start at the
+// same place of a row give a thread the same x, so it adds the 12 inner sums of
+// its nodes and only then multiplies by its a_i(x); one reduction per block
+// follows (node by node, with 24 wave reductions and 11 sines each, 2 x 128^3 in
+// float took 435 us; this takes 112, of which the reads at the card's rate are
+// 75).
 template <int QN, typename T>
-__global__ void __launch_bounds__(256) init_adjoint_kernel(const T* lam, const DevSample* samples, const Seg* segs,
-                                                           int nseg, const double* ycoef, double* partials) {
-  const int b = blockIdx.x;
-  const Seg sg = segs[find_segment(segs, nseg, b)];
-  const DevSample& sp = samples[sg.sample];
-  const int l = sp.log2n;
-  const uint32_t cell = uint32_t(b - sg.first_block) * 256u + threadIdx.x;
-  double u[3];
-  Basis bs;
-  initial_velocity(cell, l, sp.u0, sp.amp, ycoef + size_t(sg.sample) * 24, u, bs);
-  const T* lb = lam + sp.offset;
-  double ub[3] = {0.0, 0.0, 0.0};
-  for_vel<QN>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    const double li = double(ld(lb + size_t(plane_of<QN>(i)) * sp.pstride, cell)) * weight<QN>(i);
-    const double cu = double(cx(i)) * u[0] + double(cy(i)) * u[1] + double(cz(i)) * u[2];
-    ub[0] += li * (3.0 * cx(i) + 9.0 * cu * cx(i) - 3.0 * u[0]);
-    ub[1] += li * (3.0 * cy(i) + 9.0 * cu * cy(i) - 3.0 * u[1]);
-    ub[2] += li * (3.0 * cz(i) + 9.0 * cu * cz(i) - 3.0 * u[2]);
-  });
-  const double scale = sp.amp * sp.u0 * 0.125;
+__global__ void __launch_bounds__(256) init_adjoint_kernel(const T* __restrict__ lam, const DevSample* __restrict__ samples, const Seg* __restrict__ segs,
+                                                           int nseg, int per, const double* __restrict__ ycoef, double* __restrict__ partials) {
+  __shared__ double2 sc[kMaxN];
   __shared__ double sh[4][24];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int p = 0; p < 24; ++p) {
-    const int al = p >> 3, i = (p >> 2) & 1, j = (p >> 1) & 1, k = p & 1;
-    double v = scale * ub[al] * bs.a[0][i] * bs.a[1][j] * bs.a[2][k];
-    v = wave_sum(v);
-    if (lane == 0) sh[wave][p] = v;
-  }
-  __syncthreads();
-  if (threadIdx.x < 24) {
-    const int p = threadIdx.x;
-    partials[size_t(b) * 24 + p] = ((sh[0][p] + sh[1][p]) + sh[2][p]) + sh[3][p];
+  int table_n = 0;
+  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
+    const Seg sg = segs[k];
+    const int first = blockIdx.x * per, last = first + per < sg.nblocks ? first + per : sg.nblocks;
+    if (first >= last) continue;
+    const DevSample& sp = samples[sg.sample];
+    const int l = sp.log2n, n = 1 << l, msk = n - 1;
+    if (n != table_n) {
+      __syncthreads();
+      make_axis_table(sc, n);
+      __syncthreads();
+      table_n = n;
+    }
+    const double* yc = ycoef + size_t(sg.sample) * 24;
+    const T* lb = lam + sp.offset;
+    double acc[24];
+#pragma unroll
+    for (int p = 0; p < 24; ++p) acc[p] = 0.0;
+    const int phases = n > 256 ? n / 256 : 1;  // groups per row
+    for (int phase = 0; phase < phases; ++phase) {
+      double in[3][4];
+#pragma unroll
+      for (int q = 0; q < 12; ++q) in[q >> 2][q & 3] = 0.0;
+      const int b0 = first + ((phase - first) & (phases - 1));
+      const int x = int(uint32_t(b0) * 256u + threadIdx.x) & msk;
+      const double2 x1 = sc[x], x2 = sc[(2 * x) & msk];
+      for (int b = b0; b < last; b += phases) {
+        const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
+        T g[Q];  // all loads in flight before the first is used
+        for_vel<QN>([&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          g[i] = ld(lb + size_t(plane_of<QN>(i)) * sp.pstride, cell);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        const int y = int(cell >> l) & msk, z = int(cell >> (2 * l));
+        const double2 y2 = sc[(2 * y) & msk], z2 = sc[(2 * z) & msk];
+        double u[3];
+        initial_velocity(x1, x2, sc[y], y2, sc[z], z2, sp.u0, sp.amp, yc, u);
+        // ub = sum_i li (3 c_i + 9 (c_i.u) c_i - 3 u), li = w_i lambda_i
+        double sum = 0.0, l1[3] = {0.0, 0.0, 0.0}, l2[3] = {0.0, 0.0, 0.0};
+        for_vel<QN>([&](auto ic) {
+          constexpr int i = decltype(ic)::value;
+          const double li = double(g[i]) * weight<QN>(i);
+          sum += li;
+          if constexpr (nonzeros(i) > 0) {
+            const double lcu = li * cdot<i>(u[0], u[1], u[2]);
+            if constexpr (cx(i) != 0) { l1[0] += cx(i) * li; l2[0] += cx(i) * lcu; }
+            if constexpr (cy(i) != 0) { l1[1] += cy(i) * li; l2[1] += cy(i) * lcu; }
+            if constexpr (cz(i) != 0) { l1[2] += cz(i) * li; l2[2] += cz(i) * lcu; }
+          }
+        });
+        const double jk[4] = {y2.x * z2.x, y2.x * z2.y, y2.y * z2.x, y2.y * z2.y};
+#pragma unroll
+        for (int al = 0; al < 3; ++al) {
+          const double ub = 3.0 * l1[al] + 9.0 * l2[al] - 3.0 * u[al] * sum;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) in[al][q] += ub * jk[q];
+        }
+      }
+#pragma unroll
+      for (int al = 0; al < 3; ++al)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          acc[8 * al + q] += x2.x * in[al][q];
+          acc[8 * al + 4 + q] += x2.y * in[al][q];
+        }
+    }
+    const double scale = sp.amp * sp.u0 * 0.125;
+#pragma unroll
+    for (int p = 0; p < 24; ++p) {
+      const double v = wave_sum(acc[p]);
+      if (lane == 0) sh[wave][p] = scale * v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 24) {
+      const int p = threadIdx.x;
+      partials[size_t(sg.first_block + first) * 24 + p] = ((sh[0][p] + sh[1][p]) + sh[2][p]) + sh[3][p];
+    }
+    __syncthreads();
   }
 }
 
-__global__ void __launch_bounds__(256) init_adjoint_finalize_kernel(const double* partials, const Seg* segs,
-                                                                    const DevSample* samples, const double* pmat,
-                                                                    double* dJdY) {
+// The rows of a sample's blocks (one in `per`), added by 40 threads per
+// parameter in fixed order (one parameter after the other, over the partials of
+// every 256 nodes: 184 us at 2 x 128^3, this 8).
+constexpr int kInitParts = 40;
+
+__global__ void __launch_bounds__(24 * kInitParts) init_adjoint_finalize_kernel(const double* partials,
+                                                                                const Seg* segs, int per,
+                                                                                const DevSample* samples,
+                                                                                const double* pmat, double* dJdY) {
   const Seg sg = segs[blockIdx.x];
-  __shared__ double red[256];
+  __shared__ double red[kInitParts][24];
   __shared__ double dprime[24];
-  for (int p = 0; p < 24; ++p) {
+  const int p = threadIdx.x % 24, part = threadIdx.x / 24;
+  {
     double acc = 0.0;
-    for (int k = threadIdx.x; k < sg.nblocks; k += 256) acc += partials[size_t(sg.first_block + k) * 24 + p];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-      if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) dprime[p] = red[0];
-    __syncthreads();
+    const int rows = (sg.nblocks + per - 1) / per;
+#pragma unroll 4
+    for (int k = part; k < rows; k += kInitParts)
+      acc += partials[(size_t(sg.first_block) + size_t(k) * per) * 24 + p];
+    red[part][p] = acc;
   }
+  __syncthreads();
+  if (threadIdx.x < 24) {
+    double acc = 0.0;
+    for (int k = 0; k < kInitParts; ++k) acc += red[k][threadIdx.x];
+    dprime[threadIdx.x] = acc;
+  }
+  __syncthreads();
   if (threadIdx.x < 24) {
     const int q = threadIdx.x;
     double v = dprime[q];
     if (samples[sg.sample].project) {
       // Y' = P Y, so dJ/dY = P^T dJ/dY'
       v = 0.0;
-      for (int p = 0; p < 24; ++p) v += pmat[p * 24 + q] * dprime[p];
+      for (int r = 0; r < 24; ++r) v += pmat[r * 24 + q] * dprime[r];
     }
     dJdY[size_t(sg.sample) * 24 + q] = v;
   }
@@ -656,18 +767,35 @@ hipError_t launch_step2(int q, int precision, const Step2Launch& L, hipStream_t 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_record_finalize(const double* partials, const Seg* segs, int32_t nseg, const DevSample* samples,
-                                  double* out, hipStream_t s) {
+hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nseg, int32_t most_blocks,
+                                  const DevSample* samples, double* out, hipStream_t s) {
+  if (most_blocks > kRecordChunk) {
+    const dim3 grid(unsigned((most_blocks + kRecordChunk - 1) / kRecordChunk), unsigned(std::min(nseg, kMaxGridY)));
+    hipLaunchKernelGGL(record_chunk_kernel, grid, dim3(256), 0, s, partials, segs, nseg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(record_finalize_kernel, dim3(nseg), dim3(256), 0, s, partials, segs, samples, out);
   return hipGetLastError();
 }
 
+namespace {
+// Groups of 256 nodes per block of the kernels of the initial data: enough blocks
+// to fill the card first, then up to 16 groups, which share a block's table of
+// sines and its reduction.
+int groups_per_block(int32_t total_blocks) { return std::max(1, std::min(16, total_blocks / 2048)); }
+dim3 group_grid(int32_t most_blocks, int per, int32_t nseg) {
+  return dim3(unsigned((most_blocks + per - 1) / per), unsigned(std::min(nseg, kMaxGridY)));
+}
+}  // namespace
+
 hipError_t launch_init(int q, int precision, void* pop, const DevSample* samples, const Seg* segs, int32_t nseg,
-                       int32_t total_blocks, const double* ycoef, hipStream_t s) {
+                       int32_t total_blocks, int32_t most_blocks, const double* ycoef, hipStream_t s) {
+  const int per = groups_per_block(total_blocks);
   return dispatch(q, precision, [&](auto qc, auto tc) {
     using T = decltype(tc);
-    hipLaunchKernelGGL((init_kernel<decltype(qc)::value, T>), dim3(total_blocks), dim3(256), 0, s,
-                       static_cast<T*>(pop), samples, segs, nseg, ycoef);
+    hipLaunchKernelGGL((init_kernel<decltype(qc)::value, T>), group_grid(most_blocks, per, nseg), dim3(256), 0, s,
+                       static_cast<T*>(pop), samples, segs, nseg, per, ycoef);
     return hipGetLastError();
   });
 }
@@ -795,20 +923,22 @@ hipError_t launch_adjoint_step(int q, int precision, const void* state, const vo
 }
 
 hipError_t launch_init_adjoint(int q, int precision, const void* lam, const DevSample* samples, const Seg* segs,
-                               int32_t nseg, int32_t total_blocks, const double* ycoef, double* partials,
-                               hipStream_t s) {
+                               int32_t nseg, int32_t total_blocks, int32_t most_blocks, const double* ycoef,
+                               double* partials, hipStream_t s) {
+  const int per = groups_per_block(total_blocks);
   return dispatch(q, precision, [&](auto qc, auto tc) {
     using T = decltype(tc);
-    hipLaunchKernelGGL((init_adjoint_kernel<decltype(qc)::value, T>), dim3(total_blocks), dim3(256), 0, s,
-                       static_cast<const T*>(lam), samples, segs, nseg, ycoef, partials);
+    hipLaunchKernelGGL((init_adjoint_kernel<decltype(qc)::value, T>), group_grid(most_blocks, per, nseg), dim3(256), 0, s,
+                       static_cast<const T*>(lam), samples, segs, nseg, per, ycoef, partials);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_init_adjoint_finalize(const double* partials, const Seg* segs, int32_t nseg,
+hipError_t launch_init_adjoint_finalize(const double* partials, const Seg* segs, int32_t nseg, int32_t total_blocks,
                                         const DevSample* samples, const double* pmat, double* dJdY,
                                         hipStream_t s) {
-  hipLaunchKernelGGL(init_adjoint_finalize_kernel, dim3(nseg), dim3(256), 0, s, partials, segs, samples, pmat, dJdY);
+  hipLaunchKernelGGL(init_adjoint_finalize_kernel, dim3(nseg), dim3(24 * kInitParts), 0, s, partials, segs,
+                     groups_per_block(total_blocks), samples, pmat, dJdY);
   return hipGetLastError();
 }
 
