@@ -44,7 +44,8 @@ int ilog2(int v) {
 }
 bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
-constexpr int kMinBlock = 128;        // smallest collide-and-stream block
+constexpr int kMinBlock = 128;        // smallest collide-and-stream block, which small launches take
+constexpr int64_t kSmallNodes = 1 << 18;
 constexpr int kAuxBlock = 256;        // block of the auxiliary kernels
 constexpr int kMaxTables = 128;       // launch tables kept in the workspace
 constexpr size_t kHeaderBytes = 4096; // checkpoint header
@@ -88,8 +89,10 @@ std::vector<double> projection_matrix() {
 struct Table {
   size_t offset = 0;         // byte offset of the Seg array in the table pool
   int nseg = 0;
+  int block = 0;
   int total_blocks = 0;
   int most_blocks = 0;       // of one segment
+  UniformSegs uniform{};     // the table as kernel arguments, where its segments allow it
   std::vector<Seg> host;     // persistent host copy (source of the upload)
 };
 
@@ -136,6 +139,7 @@ struct mclbm_ctx {
 
   // launch shape
   int block = 256;
+  bool block_chosen = false;  // by mclbm_set_launch or mclbm_autotune: small launches keep it too
   int xcd_remap = 0;
   int buffer_addr = 1;       // buffer-resource addressing where every sample fits
   int nontemporal = 1;       // non-temporal population loads and stores
@@ -293,6 +297,27 @@ mclbm_status reserve_tables(mclbm_ctx* c, int count) {
   return MCLBM_OK;
 }
 
+// The segments as arguments, if they are consecutive samples of one resolution
+// (whose populations then follow each other at one distance) and one parity.
+UniformSegs uniform_segs(const mclbm_ctx* c, const std::vector<Seg>& segs) {
+  UniformSegs u{};
+  if (segs.empty()) return u;
+  const DevSample& h = c->h_samples[segs[0].sample];
+  for (size_t k = 1; k < segs.size(); ++k)
+    if (segs[k].sample != segs[0].sample + int(k) || c->h_samples[segs[k].sample].n != h.n ||
+        segs[k].parity != segs[0].parity)
+      return u;
+  u.on = 1;
+  u.sample0 = segs[0].sample;
+  u.shift = ilog2(segs[0].nblocks);
+  u.log2n = h.log2n;
+  u.parity = segs[0].parity;
+  u.pstride = h.pstride;
+  u.offset0 = h.offset;
+  u.stride = align_up(size_t(c->q) * h.pstride * c->elem) / c->elem;
+  return u;
+}
+
 // Launch table for the samples active at `tick` (stride divides tick), with
 // their AA parities; `all` forces every sample (init, reductions, adjoint);
 // `among`, if given, names the samples (by a flag each) it is limited to.
@@ -327,8 +352,10 @@ mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool par
   Table t;
   t.offset = c->table_next;
   t.nseg = int(segs.size());
+  t.block = block;
   t.total_blocks = first;
   for (const Seg& g : segs) t.most_blocks = std::max(t.most_blocks, int(g.nblocks));
+  t.uniform = uniform_segs(c, segs);
   t.host = segs;
   c->table_next += slot;
   if (!segs.empty()) {
@@ -344,15 +371,30 @@ const Seg* table_ptr(mclbm_ctx* c, const Table* t) {
   return reinterpret_cast<const Seg*>(reinterpret_cast<const char*>(c->d_tables) + t->offset);
 }
 
+// Threads per block of a single step over the samples active at `tick`: the
+// launch shape's, except that launches of fewer than kSmallNodes nodes, which do
+// not fill the card with 256-thread blocks, take 128 unless the caller chose a
+// shape (us per tick with 256 / 128 threads: one 32^3 sample FP64 7.0 / 5.0,
+// FP32 5.5 / 4.5; six 32^3 18.3 / 13.8 and 10.0 / 8.3; one 64^3 19.2 / 19.9 and
+// 9.2 / 9.4; 64 threads are within 0.3 us of 128 below and behind it above).
+int step_block(const mclbm_ctx* c, int64_t tick, bool all, const std::vector<char>* among = nullptr) {
+  if (c->block_chosen || c->exact_gamma) return c->block;
+  int64_t nodes = 0;
+  for (int s = 0; s < c->m && nodes < kSmallNodes; ++s)
+    if ((all || tick % c->desc[s].stride == 0) && (!among || (*among)[s])) nodes += c->cells(s);
+  return nodes < kSmallNodes ? kMinBlock : c->block;
+}
+
 StepLaunch make_launch(mclbm_ctx* c, const Table* t, void* pop, void* dst) {
   StepLaunch L;
   L.pop = pop;
   L.dst = dst;
   L.samples = c->d_samples;
   L.segs = table_ptr(c, t);
+  L.uniform = t->uniform;
   L.nseg = t->nseg;
   L.total_blocks = t->total_blocks;
-  L.block = c->block;
+  L.block = t->block;
   L.xcd_remap = c->xcd_remap;
   L.flags = c->d_flags;
   L.partials = c->d_partials;
@@ -378,7 +420,7 @@ hipEvent_t next_event(mclbm_ctx* c) {
 // optionally fused reductions.
 mclbm_status run_tick(mclbm_ctx* c, double* record_out, const std::vector<char>* among = nullptr) {
   const Table* t = nullptr;
-  mclbm_status st = get_table(c, c->tick, false, c->block, false, &t, among);
+  mclbm_status st = get_table(c, c->tick, false, step_block(c, c->tick, false, among), false, &t, among);
   if (st != MCLBM_OK) return st;
   if (t->nseg > 0) {
     StepLaunch L = make_launch(c, t, c->pop, nullptr);
@@ -425,7 +467,7 @@ mclbm_status run_graph(mclbm_ctx* c) {
     std::vector<int64_t> steps0 = c->steps;
     for (int64_t k = 0; k < len; ++k) {
       const Table* t = nullptr;
-      mclbm_status st = get_table(c, c->tick, false, c->block, false, &t);
+      mclbm_status st = get_table(c, c->tick, false, step_block(c, c->tick, false), false, &t);
       if (st != MCLBM_OK) return st;
       for (const Seg& g : t->host) c->steps[g.sample] += 1;
       c->tick += 1;
@@ -884,7 +926,7 @@ mclbm_status mclbm_reduce(mclbm_ctx* c, double* red_dev) {
   if (st != MCLBM_OK) return st;
   if (!red_dev) return fail(MCLBM_ERR_ARG, "red_dev is NULL");
   const Table* t = nullptr;
-  st = get_table(c, c->tick, true, c->block, false, &t);
+  st = get_table(c, c->tick, true, step_block(c, c->tick, true), false, &t);
   if (st != MCLBM_OK) return st;
   StepLaunch L = make_launch(c, t, c->pop, nullptr);
   HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
@@ -1002,6 +1044,13 @@ size_t mclbm_backward_work_bytes(const mclbm_ctx* c, int32_t ckpt_every) {
   return size_t(ckpt_every) * c->state_bytes + 2 * c->state_bytes + partials + records;
 }
 
+// Threads per block of a reverse step, by the same reasoning as step_block.
+static int adjoint_block(const mclbm_ctx* c) {
+  int64_t nodes = 0;
+  for (int s = 0; s < c->m && nodes < kSmallNodes; ++s) nodes += c->cells(s);
+  return nodes < kSmallNodes ? kMinBlock : kAuxBlock;
+}
+
 static mclbm_status check_adjoint(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every) {
   mclbm_status st = check_ctx(c, true);
   if (st != MCLBM_OK) return st;
@@ -1072,7 +1121,7 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
 
   if (ke_dev) {
     const Table* t = nullptr;
-    st = get_table(c, c->tick, true, c->block, false, &t);
+    st = get_table(c, c->tick, true, step_block(c, c->tick, true), false, &t);
     if (st != MCLBM_OK) return st;
     StepLaunch L = make_launch(c, t, c->pop, nullptr);
     HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
@@ -1080,7 +1129,7 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
     HIP_TRY(launch_extract(records, c->m, 4, ke_dev, c->stream));
   }
 
-  st = reserve_tables(c, 3);       // the three tables below are held together
+  st = reserve_tables(c, 4);       // the four tables below are held together
   if (st != MCLBM_OK) return st;
   const Table* aux = nullptr;      // every sample, live parities (seed)
   st = get_table(c, c->tick, true, kAuxBlock, false, &aux);
@@ -1090,8 +1139,11 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
   const Table* nat = nullptr;      // every sample, natural layout
   st = get_table(c, 0, true, kAuxBlock, true, &nat);
   if (st != MCLBM_OK) return st;
+  const Table* rev = nullptr;      // reverse steps
+  st = get_table(c, 0, true, adjoint_block(c), true, &rev);
+  if (st != MCLBM_OK) return st;
   const Table* push = nullptr;     // push steps use the collide kernel's block
-  st = get_table(c, 0, true, c->block, true, &push);
+  st = get_table(c, 0, true, step_block(c, 0, true), true, &push);
   if (st != MCLBM_OK) return st;
 
   const int32_t buffer_ok = make_launch(c, nat, c->pop, nullptr).buffer_ok;
@@ -1109,8 +1161,8 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
       HIP_TRY(launch_step(c->q, c->precision, kPush, L, c->stream));
     }
     for (int64_t n = n1 - 1; n >= n0; --n) {
-      HIP_TRY(launch_adjoint_step(c->q, c->precision, state_at(n), lam[cur], lam[1 - cur], c->d_samples, table_ptr(c, nat),
-                                  nat->nseg, nat->total_blocks, buffer_ok, c->exact_gamma, c->stream));
+      HIP_TRY(launch_adjoint_step(c->q, c->precision, state_at(n), lam[cur], lam[1 - cur], c->d_samples, table_ptr(c, rev),
+                                  rev->uniform, rev->nseg, rev->total_blocks, rev->block, buffer_ok, c->exact_gamma, c->stream));
       cur = 1 - cur;
     }
   }
@@ -1138,7 +1190,7 @@ mclbm_status mclbm_step_vjp(mclbm_ctx* c, const double* lam_dev, double* out_dev
   st = get_table(c, c->tick, true, kAuxBlock, false, &live);
   if (st != MCLBM_OK) return st;
   const Table* nat = nullptr;      // every sample, natural layout
-  st = get_table(c, 0, true, kAuxBlock, true, &nat);
+  st = get_table(c, 0, true, adjoint_block(c), true, &nat);
   if (st != MCLBM_OK) return st;
   HIP_TRY(launch_canonical_copy(c->q, c->precision, c->pop, state, c->d_samples, table_ptr(c, live), live->nseg,
                                 live->total_blocks, c->stream));
@@ -1148,8 +1200,8 @@ mclbm_status mclbm_step_vjp(mclbm_ctx* c, const double* lam_dev, double* out_dev
     off += size_t(c->q) * size_t(c->cells(s));
   }
   const int32_t buffer_ok = make_launch(c, nat, c->pop, nullptr).buffer_ok;
-  HIP_TRY(launch_adjoint_step(c->q, c->precision, state, lam_in, lam_out, c->d_samples, table_ptr(c, nat), nat->nseg,
-                              nat->total_blocks, buffer_ok, c->exact_gamma, c->stream));
+  HIP_TRY(launch_adjoint_step(c->q, c->precision, state, lam_in, lam_out, c->d_samples, table_ptr(c, nat), nat->uniform, nat->nseg,
+                              nat->total_blocks, nat->block, buffer_ok, c->exact_gamma, c->stream));
   off = 0;
   for (int s = 0; s < c->m; ++s) {
     HIP_TRY(launch_get_adjoint(c->q, c->precision, lam_out, c->d_samples, s, c->desc[s].n, out_dev + off, c->stream));
@@ -1354,6 +1406,7 @@ mclbm_status mclbm_set_launch(mclbm_ctx* c, int32_t block_threads, int32_t xcd_r
   if (nontemporal != 0 && nontemporal != 1) return fail(MCLBM_ERR_ARG, "nontemporal must be 0 or 1");
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->block = block_threads;
+  c->block_chosen = true;
   c->xcd_remap = xcd_remap;
   c->buffer_addr = buffer_addressing;
   c->nontemporal = nontemporal;
@@ -1386,6 +1439,8 @@ mclbm_status mclbm_autotune(mclbm_ctx* c, int32_t reps, void* scratch_dev, size_
   }
   const bool timing0 = c->timing, graphs0 = c->use_graphs;
   const int b0 = c->block, x0 = c->xcd_remap, f0 = c->buffer_addr, n0 = c->nontemporal;
+  const bool chosen0 = c->block_chosen;
+  c->block_chosen = true;
   c->use_graphs = false;
   c->timing = false;
   c->single_steps = true;
@@ -1466,6 +1521,7 @@ mclbm_status mclbm_autotune(mclbm_ctx* c, int32_t reps, void* scratch_dev, size_
     // keep the error of the failed trial; put back the shape and the state
     const std::string err = g_last_error;
     c->block = b0;
+    c->block_chosen = chosen0;
     c->xcd_remap = x0;
     c->buffer_addr = f0;
     c->nontemporal = n0;

@@ -16,6 +16,7 @@ struct StepLaunch {
   void* dst;                 // push mode: destination storage (natural layout)
   const DevSample* samples;
   const Seg* segs;
+  UniformSegs uniform;       // the same table as arguments, where it can be put so
   int32_t nseg;
   int32_t total_blocks;
   int32_t block;             // threads per block (cells per block)
@@ -113,8 +114,9 @@ hipError_t launch_get_adjoint(int q, int precision, const void* src, const DevSa
 hipError_t launch_adjoint_seed(int q, int precision, const void* pop, void* lam, const DevSample* samples,
                                const Seg* segs, int32_t nseg, int32_t total_blocks, double inv_m, hipStream_t s);
 hipError_t launch_adjoint_step(int q, int precision, const void* state, const void* lam_in, void* lam_out,
-                               const DevSample* samples, const Seg* segs, int32_t nseg, int32_t total_blocks,
-                               int32_t buffer_ok, int32_t exact_gamma, hipStream_t s);
+                               const DevSample* samples, const Seg* segs, const UniformSegs& uniform, int32_t nseg,
+                               int32_t total_blocks, int32_t block, int32_t buffer_ok, int32_t exact_gamma,
+                               hipStream_t s);
 hipError_t launch_init_adjoint(int q, int precision, const void* lam, const DevSample* samples, const Seg* segs,
                                int32_t nseg, int32_t total_blocks, int32_t most_blocks, const double* ycoef,
                                double* partials, hipStream_t s);

@@ -305,26 +305,25 @@ __global__ void __launch_bounds__(256) adjoint_seed_kernel(const T* pop, T* lam,
 // f*_i = w_i + g_i - omega ds_i - t dh_i; by the implicit function theorem
 // dt = (dF at fixed t) / D, D = sum_i dh_i^2 / f*_i, so the adjoint of t
 // reaches F's inputs (dh, ds and g directly) with weight tbar / D.
-template <int QN, typename T, bool BUF, bool EXACT>
-__global__ void __launch_bounds__(256) adjoint_step_kernel(const T* state, const T* lam_in, T* lam_out,
-                                                           const DevSample* samples, const Seg* segs, int nseg) {
-  const int b = blockIdx.x;
-  const Seg sg = segs[find_segment(segs, nseg, b)];
-  const DevSample& sp = samples[sg.sample];
-  const int l = sp.log2n;
-  const Cell c = make_cell(uint32_t(b - sg.first_block) * 256u + threadIdx.x, l);
-  const Relax<T> rp = relax_of<T>(sp);
+template <int QN, typename T, int BLOCK, bool BUF, bool EXACT>
+__global__ void __launch_bounds__(BLOCK) adjoint_step_kernel(const T* state, const T* lam_in, T* lam_out,
+                                                           const DevSample* samples, const Seg* segs,
+                                                           UniformSegs uniform, int nseg) {
+  const BlockSite site = block_site(uniform, segs, nseg, samples, blockIdx.x);
+  const int l = site.log2n;
+  const Cell c = make_cell(site.local_block * uint32_t(BLOCK) + threadIdx.x, l);
+  const Relax<T> rp = relax_of<T>(samples[site.sample]);
   // every array is streamed once per reverse step: non-temporal accesses
   using Planes = typename std::conditional<BUF, BufPlanes<T, true, QN>, PtrPlanes<T, true, QN>>::type;
-  const Planes st_in(const_cast<T*>(state) + sp.offset, sp.pstride);
-  const Planes lam_src(const_cast<T*>(lam_in) + sp.offset, sp.pstride);
-  const Planes lam_dst(lam_out + sp.offset, sp.pstride);
+  const Planes st_in(const_cast<T*>(state) + site.offset, site.pstride);
+  const Planes lam_src(const_cast<T*>(lam_in) + site.offset, site.pstride);
+  const Planes lam_dst(lam_out + site.offset, site.pstride);
 
   // lambda is pulled from x + c_i; rows longer than a wave (and held whole by
   // the block) are read at the node's own x and shifted by lane exchange
   const uint32_t n = 1u << l;
-  const bool rows = n > 64u && n <= 256u;
-  __shared__ EdgeLds<T, 256> edge;
+  const bool rows = n > 64u && n <= uint32_t(BLOCK);
+  __shared__ EdgeLds<T, BLOCK> edge;
   T g[Q], nu[Q];
   if (rows) {
     for_vel<QN>([&](auto ic) {
@@ -332,7 +331,7 @@ __global__ void __launch_bounds__(256) adjoint_step_kernel(const T* state, const
       g[i] = st_in.load(i, c.cell);
       nu[i] = lam_src.load(i, neighbour_yz<i, +1>(c));
     });
-    row_shift<QN, -1, 256>(nu, edge, n);
+    row_shift<QN, -1, BLOCK>(nu, edge, n);
   } else {
     for_vel<QN>([&](auto ic) {
       constexpr int i = decltype(ic)::value;
@@ -896,29 +895,49 @@ hipError_t launch_adjoint_seed(int q, int precision, const void* pop, void* lam,
   });
 }
 
+namespace {
+template <int QN, typename T, int BLOCK>
+hipError_t launch_adjoint_step_t(const T* a, const T* b, T* o, const DevSample* samples, const Seg* segs,
+                                 const UniformSegs& uniform, int32_t nseg, int32_t total_blocks, int32_t buffer_ok,
+                                 int32_t exact_gamma, hipStream_t s) {
+  const dim3 grid(total_blocks), blk(BLOCK);
+  if (exact_gamma) {
+    // FP64 only (the host refuses FP32): see mclbm_backward
+    if constexpr (!std::is_same<T, double>::value) return hipErrorInvalidValue;
+    else if (buffer_ok)
+      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, true>), grid, blk, 0, s, a, b, o, samples, segs,
+                         uniform, nseg);
+    else
+      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, true>), grid, blk, 0, s, a, b, o, samples, segs,
+                         uniform, nseg);
+  } else if (buffer_ok) {
+    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, false>), grid, blk, 0, s, a, b, o, samples, segs,
+                       uniform, nseg);
+  } else {
+    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, false>), grid, blk, 0, s, a, b, o, samples, segs,
+                       uniform, nseg);
+  }
+  return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_adjoint_step(int q, int precision, const void* state, const void* lam_in, void* lam_out,
-                               const DevSample* samples, const Seg* segs, int32_t nseg, int32_t total_blocks,
-                               int32_t buffer_ok, int32_t exact_gamma, hipStream_t s) {
+                               const DevSample* samples, const Seg* segs, const UniformSegs& uniform, int32_t nseg,
+                               int32_t total_blocks, int32_t block, int32_t buffer_ok, int32_t exact_gamma,
+                               hipStream_t s) {
   return dispatch(q, precision, [&](auto qc, auto tc) {
     constexpr int QN = decltype(qc)::value;
     using T = decltype(tc);
     const T* a = static_cast<const T*>(state);
     const T* b = static_cast<const T*>(lam_in);
     T* o = static_cast<T*>(lam_out);
-    const dim3 grid(total_blocks), blk(256);
-    if (exact_gamma) {
-      // FP64 only (the host refuses FP32): see mclbm_backward
-      if constexpr (!std::is_same<T, double>::value) return hipErrorInvalidValue;
-      else if (buffer_ok)
-        hipLaunchKernelGGL((adjoint_step_kernel<QN, T, true, true>), grid, blk, 0, s, a, b, o, samples, segs, nseg);
-      else
-        hipLaunchKernelGGL((adjoint_step_kernel<QN, T, false, true>), grid, blk, 0, s, a, b, o, samples, segs, nseg);
-    } else if (buffer_ok) {
-      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, true, false>), grid, blk, 0, s, a, b, o, samples, segs, nseg);
-    } else {
-      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, false, false>), grid, blk, 0, s, a, b, o, samples, segs, nseg);
-    }
-    return hipGetLastError();
+    if (block == 128)
+      return launch_adjoint_step_t<QN, T, 128>(a, b, o, samples, segs, uniform, nseg, total_blocks, buffer_ok,
+                                               exact_gamma, s);
+    if (block == 256)
+      return launch_adjoint_step_t<QN, T, 256>(a, b, o, samples, segs, uniform, nseg, total_blocks, buffer_ok,
+                                               exact_gamma, s);
+    return hipErrorInvalidValue;
   });
 }
 

@@ -92,6 +92,20 @@ struct Seg {
   int32_t parity;         // steps taken so far, modulo 2 (AA layout of the state)
 };
 
+// A launch table whose segments are consecutive samples of one resolution and
+// parity, as kernel arguments: a block then finds its nodes without reading the
+// table and the sample first, two dependent loads that a small launch waits for.
+struct UniformSegs {
+  int32_t on;             // 0: use the table
+  int32_t sample0;
+  int32_t shift;          // blocks per sample, log2
+  int32_t log2n;
+  int32_t parity;
+  uint32_t pstride;
+  uint64_t offset0;       // DevSample::offset of sample0
+  uint64_t stride;        // elements from one sample's populations to the next
+};
+
 // Reduction record layout (doubles per sample).
 constexpr int kRecord = 8;  // mass, jx, jy, jz, ke, gamma_min, gamma_max, gamma_mean
 

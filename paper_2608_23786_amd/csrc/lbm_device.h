@@ -987,6 +987,37 @@ __host__ __device__ __forceinline__ int find_segment(const Seg* segs, int nseg, 
   return lo;
 }
 
+// a value that is the same in every lane, in scalar registers
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) {
+  return uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
+}
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+  return (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))))) << 32) |
+         uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
+}
+
+// What a block of a step kernel works on.
+struct BlockSite {
+  int32_t sample;
+  int32_t log2n;
+  int32_t parity;
+  uint32_t local_block;   // block within the sample
+  uint32_t pstride;
+  uint64_t offset;        // element offset of the sample's populations
+};
+__device__ __forceinline__ BlockSite block_site(const UniformSegs& u, const Seg* segs, int nseg,
+                                                const DevSample* samples, int b) {
+  if (u.on) {
+    const int s = b >> u.shift;
+    return {u.sample0 + s, u.log2n, u.parity, uint32_t(b - (s << u.shift)), u.pstride,
+            u.offset0 + uint64_t(s) * u.stride};
+  }
+  const Seg sg = segs[find_segment(segs, nseg, b)];
+  const DevSample& sp = samples[sg.sample];
+  return {int32_t(uniform32(sg.sample)), int32_t(uniform32(sp.log2n)), int32_t(uniform32(sg.parity)),
+          uniform32(uint32_t(b - sg.first_block)), uniform32(sp.pstride), uniform64(sp.offset)};
+}
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -56,11 +56,6 @@ struct Step2Args {
   int32_t* flags;
 };
 
-__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
-  return (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))))) << 32) |
-         uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
-}
-
 template <typename T>
 __device__ __forceinline__ T uniform_value(T v) {
   if constexpr (sizeof(T) == 4)

@@ -16,6 +16,7 @@ struct StepArgs {
   T* dst;
   const DevSample* samples;
   const Seg* segs;
+  UniformSegs uniform;
   int32_t nseg;
   int32_t total_blocks;
   int32_t xcd_remap;
@@ -27,13 +28,13 @@ struct StepArgs {
 template <int QN, typename T, int BLOCK, StepKind KIND, bool BUF, bool NT, bool EXACT = false>
 __global__ void __launch_bounds__(BLOCK) kbc_step_kernel(StepArgs<T> a) {
   const int b = remap_block(blockIdx.x, a.total_blocks, a.xcd_remap);
-  const Seg sg = a.segs[find_segment(a.segs, a.nseg, b)];
-  const DevSample& sp = a.samples[sg.sample];
-  const int l = sp.log2n;
-  const Cell c = make_cell(uint32_t(b - sg.first_block) * BLOCK + threadIdx.x, l);
+  const BlockSite site = block_site(a.uniform, a.segs, a.nseg, a.samples, b);
+  const DevSample& sp = a.samples[site.sample];
+  const int l = site.log2n;
+  const Cell c = make_cell(site.local_block * BLOCK + threadIdx.x, l);
   using Planes = typename std::conditional<BUF, BufPlanes<T, NT, QN>, PtrPlanes<T, NT, QN>>::type;
-  const Planes src(a.pop + sp.offset, sp.pstride);
-  const bool odd = (KIND != kPush) && (sg.parity & 1);
+  const Planes src(a.pop + site.offset, site.pstride);
+  const bool odd = (KIND != kPush) && (site.parity & 1);
 
   // rows longer than a wave, held whole by the block: x-shifts by lane exchange
   const uint32_t n = 1u << l;
@@ -72,12 +73,12 @@ __global__ void __launch_bounds__(BLOCK) kbc_step_kernel(StepArgs<T> a) {
     }
   }
   const CellResult<T> res = kbc_collide<QN, EXACT>(g, relax_of<T>(sp));
-  if (res.bad) a.flags[sg.sample] = 1;
+  if (res.bad) a.flags[site.sample] = 1;
 
   if constexpr (KIND == kStep || KIND == kStepRecord || KIND == kPush) {
     const bool pushes = KIND == kPush || odd;
     T* const out = KIND == kPush ? a.dst : a.pop;
-    const Planes dst(out + sp.offset, sp.pstride);
+    const Planes dst(out + site.offset, site.pstride);
     if (!pushes) {
       for_vel<QN>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
@@ -119,6 +120,7 @@ hipError_t launch_step_t(const StepLaunch& L, hipStream_t s) {
   a.dst = static_cast<T*>(L.dst);
   a.samples = L.samples;
   a.segs = L.segs;
+  a.uniform = L.uniform;
   a.nseg = L.nseg;
   a.total_blocks = L.total_blocks;
   a.xcd_remap = L.xcd_remap;
@@ -159,6 +161,7 @@ hipError_t launch_step_exact(const StepLaunch& L, hipStream_t s) {
   a.dst = static_cast<T*>(L.dst);
   a.samples = L.samples;
   a.segs = L.segs;
+  a.uniform = L.uniform;
   a.nseg = L.nseg;
   a.total_blocks = L.total_blocks;
   a.xcd_remap = L.xcd_remap;
