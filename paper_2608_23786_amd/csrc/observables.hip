@@ -32,11 +32,9 @@
 //   5. per row (f_y, f_z): the folded inverse along x (H is even in kx once
 //      y and z are folded, so its transform is real; two rows per complex
 //      transform), X(f), and the shell sums for S2.
-// Radix-2/4 decimation-in-time transforms of whole lines in LDS (padded
-// against bank conflicts), the first and last stage in registers of the
-// thread that loads or keeps a quartet of the line, twiddles by sincospi;
-// each launch hands every XCD
-// a contiguous run of blocks, so that blocks sharing cache lines share an
+// Transforms of whole lines in two factors (three at 512) held in registers,
+// with exchanges through LDS between them, twiddles by sincospi;
+// each launch hands every XCD a contiguous run of blocks, so that blocks sharing cache lines share an
 // L2. Shells hold the integer vectors (minimum image, components in
 // {-N/2+1, ..., N/2}) whose length rounds to the shell index. Every shell sum
 // is taken per line (the line folded by the magnitude of its own
@@ -57,16 +55,23 @@
 namespace mclbm {
 namespace {
 
-// Lines per block of the transforms along y and z (LDS: about LINES * N
-// complex doubles); it divides n, so it divides the n (n/2 + 1) lines of a
-// field.
-constexpr int half_lines(int n) { return n >= 512 ? 4 : (n >= 256 ? 8 : (n >= 16 ? 16 : 8)); }
+// Elements of a line that a thread holds in the transforms, and the threads per line
+constexpr int fft_elems(int n) { return n >= 512 ? 8 : (n >= 128 ? 16 : (n >= 32 ? 8 : 4)); }
+constexpr int fft_threads(int n) { return n / fft_elems(n); }
 
-// Lines per block of the z pass (its LDS holds the lines and Psi of each)
-constexpr int z_lines(int n) { return n == 128 ? 8 : half_lines(n); }
+// Lines per block of the transforms along y: 128 threads (256 from 256 on; at
+// 256 16 lines take 284 us of two samples, 8 take 299), and 128 bytes or more of
+// consecutive lines per access; it divides n, so it divides the n (n/2 + 1)
+// lines of a field.
+constexpr int y_lines(int n) { return n >= 512 ? 4 : (n == 32 ? 32 : (n >= 16 ? 16 : 8)); }
+
+// Lines per block of the z pass: its phases (loads, exchanges, shell sums) are
+// kept apart by barriers, so more and smaller blocks overlap better (us of two
+// 256^3 with 4 / 8 / 16 lines 276 / 277 / 300, of twelve 128^3 198 / 189 / 223).
+constexpr int z_lines(int n) { return n == 128 || n == 256 ? 8 : y_lines(n); }
 
 // Pairs of real lines per block of the folded inverse passes along y and x
-// (one complex transform per pair; LDS: about PAIRS * N complex doubles)
+// (one complex transform per pair)
 constexpr int cos_pairs(int n) { return n >= 512 ? 4 : (n >= 128 ? 8 : 16); }
 
 // Lines of the folded passes: (N/2 + 1)^2 per value of the other index
@@ -81,154 +86,207 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-template <int N>
-constexpr int log2_of() {
+constexpr int log2_of(int n) {
   int l = 0;
-  while ((1 << l) < N) ++l;
+  while ((1 << l) < n) ++l;
   return l;
 }
 
-template <int N>
-__device__ __forceinline__ int bitrev(int i) {
-  return int(__brev(unsigned(i)) >> (32 - log2_of<N>()));
-}
+// Transforms of whole lines, in registers but for the exchanges between their
+// factors. A line of N elements belongs to fft_threads(N) threads; thread t
+// holds elements t + m N/E, m < E = fft_elems(N), before and after (the same
+// set, so Psi can stay in registers between a forward and an inverse
+// transform). N = A B with A = E: thread t transforms its A elements
+// (n = t + B m to k1), multiplies by W_N^{t k1}, and after one exchange through
+// LDS transforms the B elements of each k1 = t + B j to k = k1 + A k2. 512 is
+// 8 x 8 x 8 with two exchanges. Against radix-4 steps of a thread's quartet,
+// with a pass over LDS after each, a 256-element line goes through LDS once
+// instead of three times: us of two samples of 256^3,
+// y 318 -> 284, z 327 -> 275; at 512 6660 -> 6020 for one sample from its
+// populations, 4650 -> 3830 from its velocity; to 128 within 2 %.
 
-// LDS slot of element p of a line (or of the twiddle table): one spare slot
-// after every 16 complex values (256 bytes), so that the bit-reversed and
-// strided accesses of a wave spread over the LDS banks instead of landing
-// on a few of them.
-__device__ __forceinline__ int lds_pos(int p) { return p + (p >> 4); }
-
-// LDS slots from one line of N complex values to the next: the padded line
-// plus one slot, an odd number of 16-byte slots, so that the lanes of a wave
-// that touch the same element of consecutive lines (the loads and stores of
-// the y and z passes, where consecutive lanes take consecutive lines to keep
-// their global accesses contiguous) fall on different banks.
+// LDS slots of a line: rows of B + 1 for the exchange (or N in natural
+// order), an odd number of 16-byte slots, so that lanes that touch the same
+// element of consecutive lines fall on different banks, as do those of one line.
 template <int N>
 constexpr int lds_line() {
-  return N + N / 16 + 1;
+  return N >= 512 ? 585 : ((fft_elems(N) * (N / fft_elems(N) + 1)) | 1);
 }
 
-// e^{sign 2 pi i k / N}, k < N/2, at tw[lds_pos(k)]
+// The same in 8-byte slots, for exchanges of one part of the values at a time
+// (half the LDS, which doubles the blocks of a CU) by LINES lines whose lanes
+// are neighbours: the lines of 32 lanes are 32 / LINES banks of 8 bytes apart,
+// and the lanes of one line take the banks between.
+template <int N, int LINES>
+constexpr int lds_half_line() {
+  const int least = N >= 512 ? 584 : fft_elems(N) * (N / fft_elems(N) + 1), step = LINES >= 32 ? 1 : 32 / LINES;
+  return (least + 31 - step) / 32 * 32 + step;
+}
+
+// e^{-2 pi i k / N}, k < N; the first quadrant computed, the others its rotations
 template <int N>
-__device__ __forceinline__ void make_twiddles(double2* tw, int sign) {
-  for (int k = threadIdx.x; k < N / 2; k += blockDim.x) {
+__device__ __forceinline__ void make_twiddles(double2* tw) {
+  for (int k = threadIdx.x; k < N / 4; k += blockDim.x) {
     double s, c;
     sincospi(2.0 * k / N, &s, &c);
-    tw[lds_pos(k)] = make_double2(c, sign * s);
+    tw[k] = make_double2(c, -s);
+    tw[k + N / 4] = make_double2(-s, -c);
+    tw[k + N / 2] = make_double2(-c, s);
+    tw[k + 3 * N / 4] = make_double2(s, c);
   }
 }
 
-// Transforms of whole lines in LDS, decimation in time (bit-reversed
-// input, radix-4 steps of two radix-2 stages, an odd number of stages
-// starting with one radix-2 stage), with the first and the last stage in
-// registers, for a thread that holds a quartet of a line: the elements r, r + N/4, r + N/2,
-// r + 3N/4 (natural order, r < N/4). The first stage of the
-// decimation-in-time transform combines exactly such a quartet: with an
-// even number of radix-2 stages, the first radix-4 step reads bit-reversed
-// positions 4j..4j+3, which hold elements r, r + N/2, r + N/4, r + 3N/4 for
-// j = bitrev(r) / 4; with an odd number, the first radix-2 stage pairs
-// (r, r + N/2) at positions 2 j1, 2 j1 + 1 (j1 = bitrev(r) / 2) and
-// (r + N/4, r + 3N/4) at 2 j2, 2 j2 + 1 (j2 = bitrev(r + N/4) / 2). The last
-// radix-4 step (span N/4) leaves, for j < N/4, the outputs j, j + N/4,
-// j + N/2, j + 3N/4 in one thread. So a quartet is loaded from memory, put
-// through the first stage and written to LDS once; the middle steps run in
-// LDS as above; the last step reads LDS once and hands the output quartet
-// back in registers. Per transform that saves two of the LDS passes.
-// sign: -1 forward, +1 inverse (the twiddle e^{sign i pi/2} of the first
-// radix-4 step is (0, sign)).
-template <int N>
-__device__ __forceinline__ void first_stage_to_lds(double2* ln, int r, const double2 (&x)[4], int sign) {
-  constexpr int LOG = log2_of<N>();
-  if constexpr ((LOG & 1) == 0) {
-    const int p = bitrev<N>(r);  // 4j
-    const double2 y0 = make_double2(x[0].x + x[2].x, x[0].y + x[2].y);
-    const double2 y1 = make_double2(x[0].x - x[2].x, x[0].y - x[2].y);
-    const double2 y2 = make_double2(x[1].x + x[3].x, x[1].y + x[3].y);
-    const double2 y3 = make_double2(x[1].x - x[3].x, x[1].y - x[3].y);
-    const double2 u3 = cmul(make_double2(0.0, double(sign)), y3);
-    ln[lds_pos(p)] = make_double2(y0.x + y2.x, y0.y + y2.y);
-    ln[lds_pos(p + 2)] = make_double2(y0.x - y2.x, y0.y - y2.y);
-    ln[lds_pos(p + 1)] = make_double2(y1.x + u3.x, y1.y + u3.y);
-    ln[lds_pos(p + 3)] = make_double2(y1.x - u3.x, y1.y - u3.y);
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+
+// a times w (SIGN -1) or its conjugate (SIGN +1)
+template <int SIGN>
+__device__ __forceinline__ double2 cmul_dir(double2 a, double2 w) {
+  return cmul(a, make_double2(w.x, SIGN < 0 ? w.y : -w.y));
+}
+
+// a times e^{SIGN i pi / 2}
+template <int SIGN>
+__device__ __forceinline__ double2 quarter_turn(double2 a) {
+  return SIGN < 0 ? make_double2(a.y, -a.x) : make_double2(-a.y, a.x);
+}
+
+// Transforms of R elements in registers, natural order in and out
+template <int R, int SIGN>
+__device__ __forceinline__ void dft(double2* x) {
+  if constexpr (R == 2) {
+    const double2 a = x[0], b = x[1];
+    x[0] = cadd(a, b);
+    x[1] = csub(a, b);
+  } else if constexpr (R == 4) {
+    const double2 s0 = cadd(x[0], x[2]), d0 = csub(x[0], x[2]);
+    const double2 s1 = cadd(x[1], x[3]), d1 = quarter_turn<SIGN>(csub(x[1], x[3]));
+    x[0] = cadd(s0, s1);
+    x[1] = cadd(d0, d1);
+    x[2] = csub(s0, s1);
+    x[3] = csub(d0, d1);
+  } else if constexpr (R == 8) {
+    constexpr double h = 0.70710678118654752440;
+    double2 e[4] = {x[0], x[2], x[4], x[6]}, o[4] = {x[1], x[3], x[5], x[7]};
+    dft<4, SIGN>(e);
+    dft<4, SIGN>(o);
+    const double2 t1 = quarter_turn<SIGN>(o[1]), t3 = quarter_turn<SIGN>(o[3]);
+    o[1] = make_double2(h * (o[1].x + t1.x), h * (o[1].y + t1.y));
+    o[2] = quarter_turn<SIGN>(o[2]);
+    o[3] = make_double2(h * (t3.x - o[3].x), h * (t3.y - o[3].y));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      x[k] = cadd(e[k], o[k]);
+      x[k + 4] = csub(e[k], o[k]);
+    }
   } else {
-    const int p1 = bitrev<N>(r), p2 = bitrev<N>(r + N / 4);  // 2 j1, 2 j2
-    ln[lds_pos(p1)] = make_double2(x[0].x + x[2].x, x[0].y + x[2].y);
-    ln[lds_pos(p1 + 1)] = make_double2(x[0].x - x[2].x, x[0].y - x[2].y);
-    ln[lds_pos(p2)] = make_double2(x[1].x + x[3].x, x[1].y + x[3].y);
-    ln[lds_pos(p2 + 1)] = make_double2(x[1].x - x[3].x, x[1].y - x[3].y);
+    static_assert(R == 16, "radix");
+    constexpr double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173, h = 0.70710678118654752440;
+    // e^{-i pi j / 8} for the products j = 0, 1, 2, 3, 4, 6, 9 of two digits
+    double2 y[4][4];
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < 4; ++n1) y[n2][n1] = x[n2 + 4 * n1];
+      dft<4, SIGN>(y[n2]);
+    }
+    const double2 w1 = make_double2(c1, -s1), w2 = make_double2(h, -h), w3 = make_double2(s1, -c1);
+    y[1][1] = cmul_dir<SIGN>(y[1][1], w1);
+    y[1][2] = cmul_dir<SIGN>(y[1][2], w2);
+    y[1][3] = cmul_dir<SIGN>(y[1][3], w3);
+    y[2][1] = cmul_dir<SIGN>(y[2][1], w2);
+    y[2][2] = quarter_turn<SIGN>(y[2][2]);
+    y[2][3] = quarter_turn<SIGN>(cmul_dir<SIGN>(y[2][3], w2));
+    y[3][1] = cmul_dir<SIGN>(y[3][1], w3);
+    y[3][2] = quarter_turn<SIGN>(cmul_dir<SIGN>(y[3][2], w2));
+    y[3][3] = cmul_dir<SIGN>(y[3][3], make_double2(-c1, s1));
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) {
+      double2 z[4] = {y[0][k1], y[1][k1], y[2][k1], y[3][k1]};
+      dft<4, SIGN>(z);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) x[k1 + 4 * k2] = z[k2];
+    }
   }
 }
 
-// The radix-4 steps between the first stage and the last (spans 4, 16, ...
-// or 2, 8, ... below N/4) over nl lines in LDS; every thread of the block
-// takes part, and the block is synchronised after each step.
-template <int N>
-__device__ __forceinline__ void radix4_steps(double2* sh, int nl, const double2* tw, int half0) {
-  for (int half = half0; half < N / 4; half <<= 2) {
-    const int sa = N / (2 * half), sb = N / (4 * half);
-    for (int b = threadIdx.x; b < nl * (N / 4); b += blockDim.x) {
-      const int l = b / (N / 4), j = b % (N / 4);
-      const int pos = j % half, grp = j / half;
-      double2* ln = sh + l * lds_line<N>();
-      const int i0 = grp * 4 * half + pos;
-      const int p0 = lds_pos(i0), p1 = lds_pos(i0 + half), p2 = lds_pos(i0 + 2 * half), p3 = lds_pos(i0 + 3 * half);
-      const double2 x0 = ln[p0], x1 = ln[p1], x2 = ln[p2], x3 = ln[p3];
-      const double2 wa = tw[lds_pos(pos * sa)];
-      const double2 t1 = cmul(wa, x1), t3 = cmul(wa, x3);
-      const double2 y0 = make_double2(x0.x + t1.x, x0.y + t1.y), y1 = make_double2(x0.x - t1.x, x0.y - t1.y);
-      const double2 y2 = make_double2(x2.x + t3.x, x2.y + t3.y), y3 = make_double2(x2.x - t3.x, x2.y - t3.y);
-      const double2 u2 = cmul(tw[lds_pos(pos * sb)], y2), u3 = cmul(tw[lds_pos((pos + half) * sb)], y3);
-      ln[p0] = make_double2(y0.x + u2.x, y0.y + u2.y);
-      ln[p2] = make_double2(y0.x - u2.x, y0.y - u2.y);
-      ln[p1] = make_double2(y1.x + u3.x, y1.y + u3.y);
-      ln[p3] = make_double2(y1.x - u3.x, y1.y - u3.y);
+// R values of a thread through LDS: x[k] to at(k), then from from(k). V double2
+// moves them in one go, V double the real parts, then the imaginary parts.
+template <int R, typename V, typename To, typename From>
+__device__ __forceinline__ void exchange(double2 (&x)[R], V* ln, bool active, To&& to, From&& from) {
+  if constexpr (std::is_same<V, double2>::value) {
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) ln[to(k)] = x[k];
     }
     __syncthreads();
-  }
-}
-
-template <int N>
-__device__ __forceinline__ void middle_steps(double2* sh, int nl, const double2* tw) {
-  radix4_steps<N>(sh, nl, tw, (log2_of<N>() & 1) ? 2 : 4);
-}
-
-// Every stage but the last of nl lines loaded into LDS in bit-reversed order
-// (the first radix-2 stage of an odd number of stages included); the block
-// is synchronised after each step.
-template <int N>
-__device__ __forceinline__ void all_but_last_steps(double2* sh, int nl, const double2* tw) {
-  constexpr int LOG = log2_of<N>();
-  if constexpr (LOG & 1) {
-    for (int b = threadIdx.x; b < nl * (N / 2); b += blockDim.x) {
-      const int l = b / (N / 2), j = b % (N / 2);
-      double2* ln = sh + l * lds_line<N>();
-      const int p0 = lds_pos(2 * j), p1 = lds_pos(2 * j + 1);
-      const double2 a = ln[p0], c = ln[p1];
-      ln[p0] = make_double2(a.x + c.x, a.y + c.y);
-      ln[p1] = make_double2(a.x - c.x, a.y - c.y);
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) x[k] = ln[from(k)];
+    }
+  } else {
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) ln[to(k)] = x[k].x;
     }
     __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) x[k].x = ln[from(k)];
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) ln[to(k)] = x[k].y;
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < R; ++k) x[k].y = ln[from(k)];
+    }
   }
-  radix4_steps<N>(sh, nl, tw, (LOG & 1) ? 2 : 1);
 }
 
-// The last radix-4 step (span N/4) for outputs j, j + N/4, j + N/2, j + 3N/4
-// of one line (j < N/4): o[m] is output j + m N/4.
-template <int N>
-__device__ __forceinline__ void last_step_from_lds(const double2* ln, int j, const double2* tw, double2 (&o)[4]) {
-  constexpr int Q4 = N / 4;
-  const double2 x0 = ln[lds_pos(j)], x1 = ln[lds_pos(j + Q4)], x2 = ln[lds_pos(j + 2 * Q4)],
-                x3 = ln[lds_pos(j + 3 * Q4)];
-  const double2 wa = tw[lds_pos(2 * j)];
-  const double2 t1 = cmul(wa, x1), t3 = cmul(wa, x3);
-  const double2 y0 = make_double2(x0.x + t1.x, x0.y + t1.y), y1 = make_double2(x0.x - t1.x, x0.y - t1.y);
-  const double2 y2 = make_double2(x2.x + t3.x, x2.y + t3.y), y3 = make_double2(x2.x - t3.x, x2.y - t3.y);
-  const double2 u2 = cmul(tw[lds_pos(j)], y2), u3 = cmul(tw[lds_pos(j + Q4)], y3);
-  o[0] = make_double2(y0.x + u2.x, y0.y + u2.y);
-  o[2] = make_double2(y0.x - u2.x, y0.y - u2.y);
-  o[1] = make_double2(y1.x + u3.x, y1.y + u3.y);
-  o[3] = make_double2(y1.x - u3.x, y1.y - u3.y);
+// The transform of the line that the calling thread shares (its LDS at ln), its
+// elements in x; every thread of the block calls it, those without a line with
+// active = false. The line's LDS must be free on entry, and is read until the
+// next barrier after the return.
+template <int N, int SIGN, typename V>
+__device__ __forceinline__ void fft_line(double2 (&x)[fft_elems(N)], int t, V* ln, const double2* tw,
+                                         bool active = true) {
+  constexpr int E = fft_elems(N);
+  if (active) {
+    dft<E, SIGN>(x);
+#pragma unroll
+    for (int k1 = 1; k1 < E; ++k1) x[k1] = cmul_dir<SIGN>(x[k1], tw[k1 * t]);
+  }
+  if constexpr (N < 512) {
+    constexpr int B = N / E, PER = E / B;
+    exchange(x, ln, active, [&](int k1) { return k1 * (B + 1) + t; },
+             [&](int k) { return (t + B * (k / B)) * (B + 1) + k % B; });
+    if (active) {
+      double2 y[E];
+#pragma unroll
+      for (int j = 0; j < PER; ++j) dft<B, SIGN>(x + j * B);
+#pragma unroll
+      for (int k = 0; k < E; ++k) y[k / B + PER * (k % B)] = x[k];
+#pragma unroll
+      for (int k = 0; k < E; ++k) x[k] = y[k];
+    }
+  } else {
+    static_assert(N == 512 && E == 8, "three factors of 8");
+    const int k1 = t & 7, hi = t >> 3;
+    exchange(x, ln, active, [&](int k) { return k * 65 + t; }, [&](int m) { return k1 * 65 + hi + 8 * m; });
+    if (active) {
+      dft<8, SIGN>(x);
+#pragma unroll
+      for (int q = 1; q < 8; ++q) x[q] = cmul_dir<SIGN>(x[q], tw[8 * hi * q]);
+    }
+    __syncthreads();
+    exchange(x, ln, active, [&](int q) { return k1 * 73 + q * 9 + hi; },
+             [&](int m) { return k1 * 73 + hi * 9 + m; });
+    if (active) dft<8, SIGN>(x);
+  }
 }
 
 // A batch of samples shares one launch: blockIdx.z is the sample's place in
@@ -240,13 +298,14 @@ __device__ __forceinline__ P* in_batch(P* p, size_t wstride) {
 }
 
 // floor(sqrt(v)) for 0 <= v < 2^24, which holds for every value the shell
-// ranges meet (n <= 1024): the float square root is within a unit of it and
-// the two loops correct it.
+// ranges meet (n <= 1024): the hardware's square root is within 2^-12 of the
+// true one there, so its floor is off by one at most, and one step back or
+// forward corrects it.
 __device__ __forceinline__ int isqrt_floor(int v) {
   if (v <= 0) return 0;
-  int r = int(sqrtf(float(v)));
-  while (r * r > v) --r;
-  while ((r + 1) * (r + 1) <= v) ++r;
+  int r = int(__builtin_amdgcn_sqrtf(float(v)));
+  r -= r * r > v ? 1 : 0;
+  r += (r + 1) * (r + 1) <= v ? 1 : 0;
   return r;
 }
 
@@ -293,21 +352,22 @@ constexpr int fwd_rows(int n) { return n >= 256 ? 2 : 512 / n; }
 // the forward transform along x of the three
 // components, kx = 0..N/2 written to h[c][(z N + y) NH + kx]. The components
 // are real, so two share one complex transform: ux + i uy of each row, and
-// uz of a pair of rows, loaded into LDS in bit-reversed order; the two
+// uz of a pair of rows, by way of LDS; the two
 // spectra of a line are separated afterwards from Z(k) and Z(N - k):
 // A(k) = (Z(k) + conj Z(N - k)) / 2, B(k) = (Z(k) - conj Z(N - k)) / 2i.
 template <int QN, typename T, int N, bool FROM_U>
 __global__ void __launch_bounds__(256) fwd_x_kernel(const T* pop, const double* u, const DevSample* samples,
                                                     int sample0, int parity, double2* h0, size_t wstride) {
   constexpr int ROWS = fwd_rows(N), PAIRS = ROWS / 2, LINES = ROWS + PAIRS;
-  constexpr int NH = N / 2 + 1, Q4 = N / 4;
+  constexpr int NH = N / 2 + 1, E = fft_elems(N), TPL = fft_threads(N);
   constexpr int LS = lds_line<N>();
+  static_assert(LINES * TPL <= 256, "one line element set per thread");
   __shared__ double2 sh[LINES * LS];
-  __shared__ double2 tw[lds_line<N / 2>()];
+  __shared__ double2 tw[N];
   const DevSample& sp = samples[sample0 + blockIdx.z];
   double2* h = in_batch(h0, wstride);
   const size_t row0 = size_t(remap_block(blockIdx.x, gridDim.x, 1)) * ROWS;
-  make_twiddles<N>(tw, -1);
+  make_twiddles<N>(tw);
   double* shd = reinterpret_cast<double*>(sh);
   for (int e = threadIdx.x; e < ROWS * N; e += 256) {
     const int r = e / N, x = e % N;
@@ -324,26 +384,31 @@ __global__ void __launch_bounds__(256) fwd_x_kernel(const T* pop, const double* 
       load_state<QN>(pop + sp.offset, sp.pstride, make_cell(cell, sp.log2n), parity & 1, g);
       node_velocity<QN>(g, ux, uy, uz);
     }
-    const int rv = lds_pos(bitrev<N>(x));
-    sh[r * LS + rv] = make_double2(ux, uy);
-    shd[2 * ((ROWS + r / 2) * LS + rv) + (r & 1)] = uz;
+    sh[r * LS + x] = make_double2(ux, uy);
+    shd[2 * ((ROWS + r / 2) * LS + x) + (r & 1)] = uz;
   }
   __syncthreads();
-  all_but_last_steps<N>(sh, LINES, tw);
-  // the last step, its outputs back into the slots it read (the same thread's)
-  for (int e = threadIdx.x; e < LINES * Q4; e += 256) {
-    const int l = e / Q4, j = e % Q4;
-    double2 o[4];
-    last_step_from_lds<N>(sh + l * LS, j, tw, o);
+  const int t = threadIdx.x % TPL;
+  const bool active = threadIdx.x < LINES * TPL;
+  double2* ln = sh + (active ? threadIdx.x / TPL : 0) * LS;
+  double2 x[E];
+  if (active) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m) sh[l * LS + lds_pos(j + m * Q4)] = o[m];
+    for (int m = 0; m < E; ++m) x[m] = ln[t + m * TPL];
+  }
+  __syncthreads();
+  fft_line<N, -1>(x, t, ln, tw, active);
+  __syncthreads();
+  if (active) {
+#pragma unroll
+    for (int m = 0; m < E; ++m) ln[t + m * TPL] = x[m];
   }
   __syncthreads();
   const size_t field = size_t(N) * N * NH;
   for (int e = threadIdx.x; e < LINES * NH; e += 256) {
     const int l = e / NH, k = e % NH;
-    const double2 z = sh[l * LS + lds_pos(k)];
-    const double2 zn = sh[l * LS + lds_pos((N - k) & (N - 1))];
+    const double2 z = sh[l * LS + k];
+    const double2 zn = sh[l * LS + ((N - k) & (N - 1))];
     const double2 a = make_double2(0.5 * (z.x + zn.x), 0.5 * (z.y - zn.y));  // (Z(k) + conj Z(N-k)) / 2
     const double2 b = make_double2(0.5 * (z.y + zn.y), 0.5 * (zn.x - z.x));  // (Z(k) - conj Z(N-k)) / 2i
     if (l < ROWS) {
@@ -357,44 +422,33 @@ __global__ void __launch_bounds__(256) fwd_x_kernel(const T* pop, const double* 
   }
 }
 
-// Pass 2: transform along y of the fields h + c * N N NH,
-// c = blockIdx.y; LINES lines (z, kx) per block, consecutive kx, a quartet of
-// a line per thread (consecutive threads take consecutive lines, so their
-// global accesses are contiguous). sign -1 forward, +1 inverse.
+// Pass 2: forward transform along y of the fields h + c * N N NH,
+// c = blockIdx.y; LINES lines (z, kx) per block, consecutive kx (consecutive
+// threads take consecutive lines, so their global accesses are contiguous).
 template <int N, int LINES>
-__global__ void __launch_bounds__(256) fft_y_kernel(double2* h0, int sign, size_t wstride) {
-  constexpr int NH = N / 2 + 1, LS = lds_line<N>(), Q4 = N / 4;
+__global__ void __launch_bounds__(LINES * fft_threads(N)) fft_y_kernel(double2* h0, size_t wstride) {
+  constexpr int NH = N / 2 + 1, LS = lds_line<N>(), E = fft_elems(N), TPL = fft_threads(N);
   __shared__ double2 sh[LINES * LS];
-  __shared__ double2 tw[lds_line<N / 2>()];
-  double2* d = in_batch(h0, wstride) + size_t(blockIdx.y) * N * N * NH;
-  make_twiddles<N>(tw, sign);
-  const int line0 = remap_block(blockIdx.x, gridDim.x, 1) * LINES;
-  for (int e = threadIdx.x; e < LINES * Q4; e += 256) {
-    const int r = e / LINES, l = e % LINES;
-    const int line = line0 + l, z = line / NH, kx = line % NH;
-    double2 x[4];
+  __shared__ double2 tw[N];
+  const int l = threadIdx.x % LINES, t = threadIdx.x / LINES;
+  const int line = remap_block(blockIdx.x, gridDim.x, 1) * LINES + l, z = line / NH, kx = line % NH;
+  double2* d = in_batch(h0, wstride) + size_t(blockIdx.y) * N * N * NH + (size_t(z) * N + t) * NH + kx;
+  double2 x[E];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) x[m] = d[(size_t(z) * N + r + m * Q4) * NH + kx];
-    first_stage_to_lds<N>(sh + l * LS, r, x, sign);
-  }
+  for (int m = 0; m < E; ++m) x[m] = d[size_t(m * TPL) * NH];
+  make_twiddles<N>(tw);
   __syncthreads();
-  middle_steps<N>(sh, LINES, tw);
-  for (int e = threadIdx.x; e < LINES * Q4; e += 256) {
-    const int j = e / LINES, l = e % LINES;
-    const int line = line0 + l, z = line / NH, kx = line % NH;
-    double2 o[4];
-    last_step_from_lds<N>(sh + l * LS, j, tw, o);
+  fft_line<N, -1>(x, t, sh + l * LS, tw);
 #pragma unroll
-    for (int m = 0; m < 4; ++m) d[(size_t(z) * N + j + m * Q4) * NH + kx] = o[m];
-  }
+  for (int m = 0; m < E; ++m) d[size_t(m * TPL) * NH] = x[m];
 }
 
-// Pass 3: LINES z-lines (y, kx) per block, a quartet of a line per thread
-// (consecutive threads on consecutive lines). The forward transform along z
+// Pass 3: LINES z-lines (y, kx) per block (consecutive threads on consecutive
+// lines). The forward transform along z
 // of each of the three fields (already transformed along x and y), one
 // field at a time in LDS, with Psi, the sum of |.|^2 over the fields, kept in
-// registers (the quartets of a thread are the same for every field, and the
-// inverse transform's first stage takes the same quartets). Psi then goes to
+// registers (a thread's elements are the same for every field, and the
+// inverse transform takes the same). |k|^2 Psi then goes to
 // the transform's LDS in natural order for the shell sums of |k|^2/2 Psi
 // over the block's lines (each line folded by |kz| and weighted by its kx
 // weight, the lines added in order) into sbins[block][kappa] and the sum of
@@ -405,150 +459,108 @@ __global__ void __launch_bounds__(256) fft_y_kernel(double2* h0, int sign, size_
 // so it writes one contiguous run. One LDS area serves all three, which
 // keeps a block at the transform's LDS.
 template <int N, int LINES>
-__global__ void __launch_bounds__(256) z_psd_kernel(const double2* h0, double* g0, double* sbins0, size_t wstride) {
-  constexpr int NH = N / 2 + 1, HALF = N / 2, LS = lds_line<N>(), Q4 = N / 4;
-  constexpr int PER = (LINES * Q4 + 255) / 256;  // quartets per thread
-  __shared__ double2 sh[LINES * LS];
-  __shared__ double tot[LINES];
-  __shared__ double2 tw[lds_line<N / 2>()];
-  // Psi of every line and the (line, shell) sums live in the transform's LDS
-  // between the forward and the inverse transforms
-  static_assert(sizeof(double) * LINES * (N + HALF + 1) <= sizeof(sh), "Psi and the line sums fit in the LDS");
-  double* psi = reinterpret_cast<double*>(sh);
-  double* part = psi + LINES * N;
+__global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const double2* h0, double* g0, double* sbins0,
+                                                                       size_t wstride) {
+  constexpr int NH = N / 2 + 1, HALF = N / 2, LS = lds_half_line<N, LINES>(), E = fft_elems(N), TPL = fft_threads(N);
+  constexpr int THREADS = LINES * TPL;
+  // Psi of every line (an odd number of doubles apart) lives in the transform's LDS
+  // between the forward and the inverse transforms, then the folded lines
+  constexpr int PS = N + 1, HP = HALF + 1;
+  constexpr int SH = LS > PS ? LS : PS;
+  __shared__ double sh[LINES * SH];
+  __shared__ double tot[(THREADS + 63) / 64], last[LINES];
+  __shared__ double2 tw[N];
+  double* const psi = sh;
   const size_t field = size_t(N) * N * NH;
-  const double2* h = in_batch(h0, wstride);
   double* g = in_batch(g0, wstride);
   double* sbins = in_batch(sbins0, wstride);
-  make_twiddles<N>(tw, -1);
   const int line0 = remap_block(blockIdx.x, gridDim.x, 1) * LINES;
-  double ps[PER][4];
+  const int l = threadIdx.x % LINES, t = threadIdx.x / LINES;
+  double* const ln = sh + l * LS;
+  const double2* d = in_batch(h0, wstride) + size_t(t) * field / N + line0 + l;   // lines are (y, kx), kx fastest
+  make_twiddles<N>(tw);
+  double ps[E];
 #pragma unroll
-  for (int k = 0; k < PER; ++k)
-#pragma unroll
-    for (int m = 0; m < 4; ++m) ps[k][m] = 0.0;
+  for (int m = 0; m < E; ++m) ps[m] = 0.0;
   for (int c = 0; c < 3; ++c) {
-    const double2* d = h + c * field;
+    double2 x[E];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e < LINES * Q4) {
-        const int r = e / LINES, l = e % LINES;
-        const int line = line0 + l, y = line / NH, kx = line % NH;
-        double2 x[4];
+    for (int m = 0; m < E; ++m) x[m] = d[m * (TPL * field / N)];
+    d += field;
+    __syncthreads();  // the twiddles are there; the field before is read
+    fft_line<N, -1>(x, t, ln, tw);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) x[m] = d[(size_t(r + m * Q4) * N + y) * NH + kx];
-        first_stage_to_lds<N>(sh + l * LS, r, x, -1);
-      }
-    }
-    __syncthreads();
-    middle_steps<N>(sh, LINES, tw);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int e = threadIdx.x + 256 * k;
-      if (e < LINES * Q4) {
-        double2 o[4];
-        last_step_from_lds<N>(sh + (e % LINES) * LS, e / LINES, tw, o);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) ps[k][m] += o[m].x * o[m].x + o[m].y * o[m].y;
-      }
-    }
-    __syncthreads();  // the next field (or Psi) overwrites sh
+    for (int m = 0; m < E; ++m) ps[m] += x[m].x * x[m].x + x[m].y * x[m].y;
   }
-  // Psi in natural order; the inverse transform's twiddles are the
-  // conjugates of the forward ones
+  __syncthreads();  // Psi overwrites sh
+  // Psi folded by |kz| with the weight |k|^2 of its mode, in two halves that are
+  // added when read: element m and element N - m (zero behind m = 0; the
+  // Nyquist value is its own partner, a half in either)
+  const int myline = line0 + l, myx = myline % NH, myy = myline / NH;
+  const double s_xy = double(myx) * myx + double(myy <= HALF ? myy : N - myy) * (myy <= HALF ? myy : N - myy);
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < LINES * Q4) {
-      const int j = e / LINES, l = e % LINES;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) psi[l * N + j + m * Q4] = ps[k][m];
-    }
+  for (int m = 0; m < E; ++m) {
+    const int k = t + m * TPL, kf = k <= HALF ? k : N - k;
+    const double w = fma(double(kf), double(kf), s_xy) * ps[m];
+    psi[l * PS + k] = k == HALF ? 0.5 * w : w;
   }
-  for (int k = threadIdx.x; k < N / 2; k += 256) tw[lds_pos(k)].y = -tw[lds_pos(k)].y;
+  if (t == 0) psi[l * PS + N] = 0.0;
+  double total = 0.0;
+#pragma unroll
+  for (int m = 0; m < E; ++m) total += ps[m];
+  total *= fold_weight(myx, HALF);
+  constexpr int LANES = THREADS >= 64 ? 64 : THREADS;
+#pragma unroll
+  for (int o = LANES / 2; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+  if (threadIdx.x % LANES == 0) tot[threadIdx.x / LANES] = total;
   __syncthreads();
-  // the total of Psi per line (R_0), one wave per line
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int l = wave; l < LINES; l += 4) {
-    const int kx = (line0 + l) % NH;
-    double total = 0.0;
-    for (int i = lane; i < N; i += 64) total += psi[l * N + i];
-    total = wave_sum(total);
-    if (lane == 0) tot[l] = fold_weight(kx, HALF) * total;
-  }
-  // the shell sums of every (line, shell) pair over all threads, each line
-  // folded by |kz|; then the block's lines added per shell in line order
-  for (int e = threadIdx.x; e < LINES * (HALF + 1); e += 256) {
-    const int l = e / (HALF + 1), r = e % (HALF + 1);
-    const int line = line0 + l, y = line / NH, kx = line % NH;
-    const int ky = y <= HALF ? y : y - N;
-    const int sxy = kx * kx + ky * ky;
-    int a, b;
-    shell_range(HALF, sxy, r, a, b);
-    const double* pl = psi + l * N;
-    double sum = 0.0;
-    for (int m = a; m <= b; ++m) {
-      double v = pl[m];
-      if (m >= 1 && m <= HALF - 1) v += pl[N - m];
-      sum += 0.5 * (double(sxy) + double(m) * m) * v;
-    }
-    part[e] = fold_weight(kx, HALF) * sum;
-  }
-  __syncthreads();
+  // the shell sums, a shell per thread: the block's lines added in order. The
+  // last shell, one too many for the threads at 128 and 256, takes a thread per line.
   const size_t blk = size_t(line0 / LINES);
-  for (int r = threadIdx.x; r <= HALF + 1; r += 256) {
+  for (int e = threadIdx.x; e < HALF + LINES; e += THREADS) {
+    const int r = e < HALF ? e : HALF, k0 = e < HALF ? 0 : e - HALF, k1 = e < HALF ? LINES : k0 + 1;
     double sum = 0.0;
-    for (int l = 0; l < LINES; ++l) sum += r == HALF + 1 ? tot[l] : part[l * (HALF + 1) + r];
-    sbins[blk * (HALF + 2) + r] = sum;
+    for (int k = k0; k < k1; ++k) {
+      const int line = line0 + k, y = line / NH, kx = line % NH;
+      const int ky = y <= HALF ? y : y - N;
+      const double* pl = psi + k * PS;
+      int a, b;
+      shell_range(HALF, kx * kx + ky * ky, r, a, b);
+      double part = 0.0;
+      for (int m = a; m <= b; ++m) part += pl[m] + pl[N - m];
+      sum += (kx == 0 || kx == HALF ? 0.5 : 1.0) * part;   // half of the mode's weight in |k|^2 / 2
+    }
+    if (e < HALF)
+      sbins[blk * (HALF + 2) + r] = sum;
+    else
+      last[k0] = sum;
+  }
+  if (threadIdx.x == 0) {
+    double sum = 0.0;
+    for (int k = 0; k < (THREADS + 63) / 64; ++k) sum += tot[k];
+    sbins[blk * (HALF + 2) + HALF + 1] = sum;
   }
   __syncthreads();  // Psi and the sums are read; the inverse overwrites sh
-  // the inverse transform of Psi along z, its first stage from the registers
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < LINES * Q4) {
-      const int j = e / LINES, l = e % LINES;
-      double2 x[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) x[m] = make_double2(ps[k][m], 0.0);
-      first_stage_to_lds<N>(sh + l * LS, j, x, +1);
-    }
+  if (threadIdx.x == 0) {
+    double sum = 0.0;
+    for (int k = 0; k < LINES; ++k) sum += last[k];
+    sbins[blk * (HALF + 2) + HALF] = sum;
   }
-  __syncthreads();
-  middle_steps<N>(sh, LINES, tw);
-  // outputs j and j + N/4 of a quartet lie in 0..N/2 - 1, and j + N/2 is N/2
-  // for j = 0; mu is 2 except at 0 and N/2
-  double gv[PER][3];
+  double2 x[E];
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < LINES * Q4) {
-      const int j = e / LINES, l = e % LINES;
-      double2 o[4];
-      last_step_from_lds<N>(sh + l * LS, j, tw, o);
-      gv[k][0] = (j == 0 ? 1.0 : 2.0) * o[0].x;
-      gv[k][1] = 2.0 * o[1].x;
-      gv[k][2] = o[2].x;
-    }
-  }
+  for (int m = 0; m < E; ++m) x[m] = make_double2(ps[m], 0.0);
+  fft_line<N, +1>(x, t, ln, tw);
   __syncthreads();  // the transform's reads are done; sh stages the output
-  constexpr int HP = HALF + 1;
-  double* stage = reinterpret_cast<double*>(sh);
-  static_assert(sizeof(double) * LINES * HP <= sizeof(sh), "the folded lines fit in the LDS");
+  // outputs 0..N/2; mu is 2 except at 0 and N/2
+  double* const stage = sh;
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < LINES * Q4) {
-      const int j = e / LINES, l = e % LINES;
-      stage[l * HP + j] = gv[k][0];
-      stage[l * HP + j + Q4] = gv[k][1];
-      if (j == 0) stage[l * HP + HALF] = gv[k][2];
-    }
+  for (int m = 0; m < E; ++m) {
+    const int f = t + m * TPL;
+    if (f <= HALF) stage[l * HP + f] = fold_weight(f, HALF) * x[m].x;
   }
   __syncthreads();
   double* out = g + size_t(line0) * HP;
-  for (int i = threadIdx.x; i < LINES * HP; i += 256) out[i] = stage[i];
+  for (int i = threadIdx.x; i < LINES * HP; i += THREADS) out[i] = stage[i];
 }
 
 // Pass 4: the folded inverse transform along y. Lines j = kx (N/2 + 1) + f_z
@@ -560,53 +572,38 @@ __global__ void __launch_bounds__(256) z_psd_kernel(const double2* h0, double* g
 // Re B(f) = (Im Z(f) + Im Z(N - f)) / 2, for f_y = 0..N/2. Lines past J
 // transform zeros and are not written.
 template <int N, int PAIRS>
-__global__ void __launch_bounds__(256) cos_y_kernel(const double* g0, double* hout0, size_t wstride) {
-  constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), Q4 = N / 4;
-  constexpr int PER = (PAIRS * Q4 + 255) / 256;
+__global__ void __launch_bounds__(PAIRS * fft_threads(N)) cos_y_kernel(const double* g0, double* hout0,
+                                                                       size_t wstride) {
+  constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), E = fft_elems(N), TPL = fft_threads(N);
+  constexpr int THREADS = PAIRS * TPL;
   __shared__ double2 sh[PAIRS * LS];
-  __shared__ double2 tw[lds_line<N / 2>()];
+  __shared__ double2 tw[N];
   const double* g = in_batch(g0, wstride);
   double* ho = in_batch(hout0, wstride);
-  make_twiddles<N>(tw, +1);
   const int j0 = remap_block(blockIdx.x, gridDim.x, 1) * 2 * PAIRS;
+  const int p = threadIdx.x % PAIRS, t = threadIdx.x / PAIRS;
+  const int ja = j0 + 2 * p, jb = ja + 1;
+  double2 x[E];
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < PAIRS * Q4) {
-      const int r = e / PAIRS, p = e % PAIRS;
-      const int ja = j0 + 2 * p, jb = ja + 1;
-      double2 x[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const size_t row = size_t(r + m * Q4) * J;
-        x[m] = make_double2(ja < J ? g[row + ja] : 0.0, jb < J ? g[row + jb] : 0.0);
-      }
-      first_stage_to_lds<N>(sh + p * LS, r, x, +1);
-    }
+  for (int m = 0; m < E; ++m) {
+    const size_t row = size_t(t + m * TPL) * J;
+    x[m] = make_double2(ja < J ? g[row + ja] : 0.0, jb < J ? g[row + jb] : 0.0);
   }
+  make_twiddles<N>(tw);
   __syncthreads();
-  middle_steps<N>(sh, PAIRS, tw);
-  // the last step, its outputs back into the slots it read (the same thread's)
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < PAIRS * Q4) {
-      const int j = e / PAIRS, p = e % PAIRS;
-      double2 o[4];
-      last_step_from_lds<N>(sh + p * LS, j, tw, o);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) sh[p * LS + lds_pos(j + m * Q4)] = o[m];
-    }
-  }
+  fft_line<N, +1>(x, t, sh + p * LS, tw);
   __syncthreads();
-  for (int e = threadIdx.x; e < HP * PAIRS; e += 256) {
-    const int f = e / PAIRS, p = e % PAIRS;
-    const int ja = j0 + 2 * p;
-    if (ja >= J) continue;
-    const double2 z = sh[p * LS + lds_pos(f)], zn = sh[p * LS + lds_pos((N - f) & (N - 1))];
+#pragma unroll
+  for (int m = 0; m < E; ++m) sh[p * LS + t + m * TPL] = x[m];
+  __syncthreads();
+  for (int e = threadIdx.x; e < HP * PAIRS; e += THREADS) {
+    const int f = e / PAIRS, pe = e % PAIRS;
+    const int j = j0 + 2 * pe;
+    if (j >= J) continue;
+    const double2 z = sh[pe * LS + f], zn = sh[pe * LS + ((N - f) & (N - 1))];
     const bool edge = f == 0 || f == HALF;  // mu = 1 and Z(N - f) = Z(f)
-    ho[size_t(f) * J + ja] = edge ? z.x : z.x + zn.x;
-    if (ja + 1 < J) ho[size_t(f) * J + ja + 1] = edge ? z.y : z.y + zn.y;
+    ho[size_t(f) * J + j] = edge ? z.x : z.x + zn.x;
+    if (j + 1 < J) ho[size_t(f) * J + j + 1] = edge ? z.y : z.y + zn.y;
   }
 }
 
@@ -624,76 +621,44 @@ __global__ void __launch_bounds__(256) cos_y_kernel(const double* g0, double* ho
 // N^6 (the sum of Psi). Rows past (N/2 + 1)^2 transform zeros and add
 // nothing.
 template <int N, int PAIRS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(PAIRS * fft_threads(N))
     cos_x_kernel(const double* hin0, const double* r00, double* rbins0, size_t wstride) {
-  constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), Q4 = N / 4, ROWS = 2 * PAIRS;
-  constexpr int PER = (PAIRS * Q4 + 255) / 256;
+  constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), ROWS = 2 * PAIRS;
+  constexpr int E = fft_elems(N), TPL = fft_threads(N), THREADS = PAIRS * TPL;
   // the transforms, then (as doubles) the rows' X values and their shell sums
   constexpr int SH = PAIRS * LS > ROWS * HP ? PAIRS * LS : ROWS * HP;
   __shared__ double2 sh[SH];
-  __shared__ double2 tw[lds_line<N / 2>()];
+  __shared__ double2 tw[N];
   const double* hin = in_batch(hin0, wstride);
   const double* r0 = in_batch(r00, wstride);
   double* rbins = in_batch(rbins0, wstride);
-  make_twiddles<N>(tw, +1);
   const int q0 = remap_block(blockIdx.x, gridDim.x, 1) * ROWS;
+  const int p = threadIdx.x % PAIRS, t = threadIdx.x / PAIRS;
+  const int qa = q0 + 2 * p, qb = qa + 1;
+  const size_t ba = size_t(qa / HP) * J + qa % HP, bb = size_t(qb / HP) * J + qb % HP;
+  double2 x[E];
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < PAIRS * Q4) {
-      const int r = e / PAIRS, p = e % PAIRS;
-      const int qa = q0 + 2 * p, qb = qa + 1;
-      const size_t ba = size_t(qa / HP) * J + qa % HP, bb = size_t(qb / HP) * J + qb % HP;
-      double2 x[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const int kx = r + m * Q4, kf = kx <= HALF ? kx : N - kx;  // the even extension
-        x[m] = make_double2(qa < J ? hin[ba + size_t(kf) * HP] : 0.0, qb < J ? hin[bb + size_t(kf) * HP] : 0.0);
-      }
-      first_stage_to_lds<N>(sh + p * LS, r, x, +1);
-    }
+  for (int m = 0; m < E; ++m) {
+    const int kx = t + m * TPL, kf = kx <= HALF ? kx : N - kx;  // the even extension
+    x[m] = make_double2(qa < J ? hin[ba + size_t(kf) * HP] : 0.0, qb < J ? hin[bb + size_t(kf) * HP] : 0.0);
   }
+  make_twiddles<N>(tw);
   __syncthreads();
-  middle_steps<N>(sh, PAIRS, tw);
-  // outputs j and j + N/4 of a quartet lie in 0..N/2 - 1, and j + N/2 is N/2
-  // for j = 0
-  double xv[PER][3][2];
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < PAIRS * Q4) {
-      const int j = e / PAIRS, p = e % PAIRS;
-      double2 o[4];
-      last_step_from_lds<N>(sh + p * LS, j, tw, o);
-      const double w0 = j == 0 ? 1.0 : 2.0;
-      xv[k][0][0] = w0 * o[0].x;
-      xv[k][0][1] = w0 * o[0].y;
-      xv[k][1][0] = 2.0 * o[1].x;
-      xv[k][1][1] = 2.0 * o[1].y;
-      xv[k][2][0] = o[2].x;
-      xv[k][2][1] = o[2].y;
-    }
-  }
+  fft_line<N, +1>(x, t, sh + p * LS, tw);
   __syncthreads();  // the transform's reads are done; sh holds the rows next
   double* xr = reinterpret_cast<double*>(sh);  // [ROWS][HP]
   double* part = xr + ROWS * HP;                // [ROWS][HP]
 #pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int e = threadIdx.x + 256 * k;
-    if (e < PAIRS * Q4) {
-      const int j = e / PAIRS, p = e % PAIRS;
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        double* row = xr + (2 * p + b) * HP;
-        row[j] = xv[k][0][b];
-        row[j + Q4] = xv[k][1][b];
-        if (j == 0) row[HALF] = xv[k][2][b];
-      }
+  for (int m = 0; m < E; ++m) {
+    const int f = t + m * TPL;
+    if (f <= HALF) {
+      xr[(2 * p) * HP + f] = fold_weight(f, HALF) * x[m].x;
+      xr[(2 * p + 1) * HP + f] = fold_weight(f, HALF) * x[m].y;
     }
   }
   __syncthreads();
   const double R0 = *r0;
-  for (int e = threadIdx.x; e < ROWS * HP; e += 256) {
+  for (int e = threadIdx.x; e < ROWS * HP; e += THREADS) {
     const int rho = e / HP, c = e % HP;
     const int q = q0 + rho;
     double sum = 0.0;
@@ -709,7 +674,7 @@ __global__ void __launch_bounds__(256)
   }
   __syncthreads();
   const size_t blk = size_t(q0 / ROWS);
-  for (int c = threadIdx.x; c <= HALF + 1; c += 256) {
+  for (int c = threadIdx.x; c <= HALF + 1; c += THREADS) {
     double sum = 0.0;
     for (int r = 0; r < ROWS && c <= HALF; ++r) sum += part[r * HP + c];
     rbins[blk * (HALF + 2) + c] = sum;
@@ -850,7 +815,7 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t sign) {
 // sign flip per value and merge instead of selects in every step.
 template <int E>
 __device__ __forceinline__ void wave_sort(double (&v)[E], int lane) {
-  static_for<1, log2_of<64 * E>() + 1>([&](auto kc) {
+  static_for<1, log2_of(64 * E) + 1>([&](auto kc) {
     constexpr int k = 1 << decltype(kc)::value;
     const uint32_t sign = k >= E && ((lane * E) & k) != 0 ? 0x80000000u : 0u;
     if constexpr (k >= E) {
@@ -1145,11 +1110,11 @@ ObsWork carve(void* work, int n) {
 template <int QN, typename T, int N, bool FROM_U>
 hipError_t observables_t(const T* pop, const double* u, const DevSample* samples, int sample0, int count, int parity,
                          void* work, double* s2, double* ek, hipStream_t s) {
-  constexpr int NH = N / 2 + 1, L = half_lines(N);
+  constexpr int NH = N / 2 + 1, LY = y_lines(N), LZ = z_lines(N);
   constexpr int ROWS_X = fwd_rows(N);
   constexpr int PC = cos_pairs(N);
   constexpr int W = N / 2 + 2;
-  static_assert(N % L == 0 && (N * N) % ROWS_X == 0, "launch shapes must tile the field");
+  static_assert(N % LY == 0 && N % LZ == 0 && (N * N) % ROWS_X == 0, "launch shapes must tile the field");
   const ObsWork w = carve(work, N);
   const size_t ws = sample_work_bytes(N);
   const unsigned z = unsigned(count);
@@ -1158,17 +1123,17 @@ hipError_t observables_t(const T* pop, const double* u, const DevSample* samples
   const int lchunks = int(chunks_of(srows)), rchunks = int(chunks_of(rrows));
   hipLaunchKernelGGL((fwd_x_kernel<QN, T, N, FROM_U>), dim3(N * N / ROWS_X, 1, z), dim3(256), 0, s, pop, u, samples,
                      sample0, parity, w.h, ws);
-  hipLaunchKernelGGL((fft_y_kernel<N, L>), dim3(lines / L, 3, z), dim3(256), 0, s, w.h, -1, ws);
-  constexpr int LZ = z_lines(N);
-  hipLaunchKernelGGL((z_psd_kernel<N, LZ>), dim3(lines / LZ, 1, z), dim3(256), 0, s, w.h, w.g, w.sbins, ws);
+  constexpr int TPL = fft_threads(N);
+  hipLaunchKernelGGL((fft_y_kernel<N, LY>), dim3(lines / LY, 3, z), dim3(LY * TPL), 0, s, w.h, ws);
+  hipLaunchKernelGGL((z_psd_kernel<N, LZ>), dim3(lines / LZ, 1, z), dim3(LZ * TPL), 0, s, w.h, w.g, w.sbins, ws);
   hipLaunchKernelGGL(shell_partial_kernel, dim3(lchunks, 1, z), dim3(256), 0, s, w.sbins, srows, W, w.psum, ws);
   hipLaunchKernelGGL(shell_count_kernel, dim3(NH), dim3(256), 0, s, N, w.cnt);
   hipLaunchKernelGGL(shell_final_kernel, dim3(W, 1, z), dim3(256), 0, s, w.psum, w.cnt, lchunks, W, N, 0, ek, w.r0,
                      ws);
   if (s2) {
     double* hr = reinterpret_cast<double*>(w.h);
-    hipLaunchKernelGGL((cos_y_kernel<N, PC>), dim3(rrows, 1, z), dim3(256), 0, s, w.g, hr, ws);
-    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(256), 0, s, hr, w.r0, w.rbins, ws);
+    hipLaunchKernelGGL((cos_y_kernel<N, PC>), dim3(rrows, 1, z), dim3(PC * TPL), 0, s, w.g, hr, ws);
+    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(PC * TPL), 0, s, hr, w.r0, w.rbins, ws);
     hipLaunchKernelGGL(shell_partial_kernel, dim3(rchunks, 1, z), dim3(256), 0, s, w.rbins, rrows, W, w.psum, ws);
     hipLaunchKernelGGL(shell_final_kernel, dim3(W, 1, z), dim3(256), 0, s, w.psum, w.cnt, rchunks, W, N, 1, s2,
                        nullptr, ws);
