@@ -543,8 +543,14 @@ int run_chunk(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   return (r.count + trips - 1) / trips;
 }
 
+// Whether passes of two pay for a run (us per tick of single steps / passes at
+// 2^20 nodes: 32^3 FP32 39.8 / 35.7, D3Q19 27.9 / 26.8; 64^3 40.1 / 36.2, 28.1 /
+// 26.7; FP64 1.13-1.38 x; at 2^24 1.12-1.57 x throughout). Not 32^3 of D3Q27 in
+// FP64, whose tile of two rows per wave does not fit the registers (62 spilled):
+// 77.5 / 105 at 2^20, 1229 / 1467 at 2^24.
 bool two_step_size(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   const int n = c->desc[r.first].n;
+  if (n == 32 && c->q == 27 && c->precision == 0) return false;
   return n <= 512 && int64_t(r.count) * n * n * n >= kTwoStepNodes;
 }
 

@@ -448,7 +448,9 @@ hipError_t launch_step2_t(const Step2Launch& L, hipStream_t s) {
   switch (L.log2n) {
     case 3: return launch_step2_tile<QN, T, 8, 8, 0, false>(L, s);
     case 4: return launch_step2_tile<QN, T, 16, 16, 0, false>(L, s);
-    case 5: return launch_step2_tile<QN, T, 32, f32 ? 32 : 16, f32 ? 0 : 1, false>(L, s);
+    case 5:
+      if constexpr (QN == 27 && !f32) return hipErrorInvalidValue;   // stays with single steps
+      else return launch_step2_tile<QN, T, 32, f32 ? 32 : 16, f32 ? 0 : 1, false>(L, s);
     case 6: return launch_step2_tile<QN, T, 64, f32 ? 16 : 8, 1, false>(L, s);
     case 7:
     case 8:

@@ -17,7 +17,8 @@ mc = pytest.importorskip("paper_2608_23786_amd")
 def _ensemble(n, m, precision, lattice, two):
     u0 = mc_inputs.diffusive_u0(n) if n >= 32 else 0.05
     ens = mc.Ensemble([mc.Sample(n, u0, 25.0 * n, 0.05, True)] * m, precision, lattice=lattice)
-    assert ens.two_step(two) == two
+    # 32^3 of D3Q27 in FP64 keeps single steps
+    assert ens.two_step(two) == (two and (n, precision, lattice) != (32, "f64", 27))
     ens.init(5)
     return ens
 
