@@ -544,6 +544,7 @@ def traffic_probe(mc, torch, ticks=4):
         ens.init(3)
         ens.set_launch(block, 0, buf, 1)
         ens.use_graphs(False)
+        ens.two_step(False)
         ens.step(ticks)
         ens.synchronize()
         print(f"[traffic-probe] D3Q{q} {m} x {n}^3 block {block} buffer {buf}: {ticks} ticks", flush=True)

@@ -126,12 +126,13 @@ size_t mclbm_workspace_bytes(int32_t m, const mclbm_sample_desc* desc, int32_t p
 mclbm_status mclbm_create(mclbm_ctx** out, int32_t m, const mclbm_sample_desc* desc, int32_t precision,
                           int32_t lattice, void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Two steps per pass over memory. With a scratch buffer set, mclbm_step (and
- * mclbm_forward_ckpt) advance runs of consecutive samples of one resolution
+/* Two steps per pass over memory. With a scratch buffer set, mclbm_step
+ * advances runs of consecutive samples of one resolution
  * and stride, between records, four steps at a time in two passes, from the
  * state to the scratch and back, each of which reads and writes the
- * populations once for two steps; the results are bitwise those of single
- * steps. mclbm_step_scratch_bytes gives the size (0 where no run of the
+ * populations once for two steps; the results are those of single steps, bit
+ * for bit in FP64 and to rounding in FP32 (mclbm_forward_ckpt keeps single
+ * steps). mclbm_step_scratch_bytes gives the size (0 where no run of the
  * ensemble is large enough to gain): up to 2 GiB for samples of at most 64^3,
  * one sample's populations above. The closed-form stabiliser only; launch
  * timing (mclbm_time_launches) and mclbm_autotune take single steps.
