@@ -48,7 +48,7 @@ constexpr int kMinBlock = 128;        // smallest collide-and-stream block, whic
 constexpr int64_t kSmallNodes = 1 << 18;
 constexpr int kAuxBlock = 256;        // block of the auxiliary kernels
 constexpr int kMaxTables = 128;       // launch tables kept in the workspace
-constexpr size_t kHeaderBytes = 4096; // checkpoint header
+constexpr size_t kHeaderBytes = 4096; // smallest checkpoint header
 constexpr uint64_t kCkptMagic = 0x4d434c424d434b50ull;
 constexpr size_t kFwdHeaderBytes = 256;  // forward checkpoints: the token of the forward that wrote them
 std::atomic<uint64_t> g_fwd_tokens{0};
@@ -170,8 +170,6 @@ struct mclbm_ctx {
   bool timing = false;
   std::vector<hipEvent_t> ev_pool;
   size_t ev_used = 0;
-
-  std::vector<char> ckpt_header;
 
   int64_t cells(int s) const { return int64_t(desc[s].n) * desc[s].n * desc[s].n; }
 };
@@ -784,7 +782,6 @@ mclbm_status mclbm_create(mclbm_ctx** out, int32_t m, const mclbm_sample_desc* d
     delete c;
     return fail(MCLBM_ERR_HIP, std::string("context upload: ") + hipGetErrorString(e));
   }
-  c->ckpt_header.assign(kHeaderBytes, 0);
   for (int s = 0; s < m; ++s) {
     if (s > 0 && desc[s].n == desc[s - 1].n && desc[s].stride == desc[s - 1].stride) c->runs.back().count += 1;
     else c->runs.push_back({s, 1});
@@ -993,7 +990,13 @@ mclbm_status mclbm_poison(mclbm_ctx* c, int32_t sample, int64_t cell, int32_t i)
   return MCLBM_OK;
 }
 
-size_t mclbm_checkpoint_bytes(const mclbm_ctx* c) { return c ? kHeaderBytes + c->state_bytes : 0; }
+// A checkpoint's header: five words and the step counter of every sample, which
+// from 508 samples on take more than kHeaderBytes.
+static size_t header_bytes(const mclbm_ctx* c) {
+  return std::max(kHeaderBytes, align_up(sizeof(int64_t) * (5 + size_t(c->m))));
+}
+
+size_t mclbm_checkpoint_bytes(const mclbm_ctx* c) { return c ? header_bytes(c) + c->state_bytes : 0; }
 
 mclbm_status mclbm_checkpoint(mclbm_ctx* c, void* dst_dev, size_t bytes) {
   mclbm_status st = check_ctx(c, true);
@@ -1010,7 +1013,7 @@ mclbm_status mclbm_checkpoint(mclbm_ctx* c, void* dst_dev, size_t bytes) {
   h[4] = c->tick;
   for (int s = 0; s < c->m; ++s) h[5 + s] = c->steps[s];
   HIP_TRY(hipMemcpy(dst_dev, h.data(), sizeof(int64_t) * h.size(), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpyAsync(static_cast<char*>(dst_dev) + kHeaderBytes, c->pop, c->state_bytes, hipMemcpyDeviceToDevice,
+  HIP_TRY(hipMemcpyAsync(static_cast<char*>(dst_dev) + header_bytes(c), c->pop, c->state_bytes, hipMemcpyDeviceToDevice,
                          c->stream));
   return MCLBM_OK;
 }
@@ -1026,7 +1029,7 @@ mclbm_status mclbm_restore(mclbm_ctx* c, const void* src_dev, size_t bytes) {
   if (h[0] != int64_t(kCkptMagic) || h[1] != c->m || h[2] != c->precision || h[3] != c->q)
     return fail(MCLBM_ERR_ARG, "checkpoint does not belong to this ensemble");
   c->generation += 1;
-  HIP_TRY(hipMemcpyAsync(c->pop, static_cast<const char*>(src_dev) + kHeaderBytes, c->state_bytes,
+  HIP_TRY(hipMemcpyAsync(c->pop, static_cast<const char*>(src_dev) + header_bytes(c), c->state_bytes,
                          hipMemcpyDeviceToDevice, c->stream));
   c->tick = h[4];
   for (int s = 0; s < c->m; ++s) c->steps[s] = h[5 + s];
