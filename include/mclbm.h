@@ -130,9 +130,10 @@ mclbm_status mclbm_create(mclbm_ctx** out, int32_t m, const mclbm_sample_desc* d
  * advances runs of consecutive samples of one resolution
  * and stride, between records, four steps at a time in two passes, from the
  * state to the scratch and back, each of which reads and writes the
- * populations once for two steps; the results are those of single steps, bit
- * for bit in FP64 and to rounding in FP32 (mclbm_forward_ckpt keeps single
- * steps). mclbm_step_scratch_bytes gives the size (0 where no run of the
+ * populations once for two steps. The populations are those of single steps,
+ * bit for bit, so they do not depend on how a run is cut into calls and
+ * records, on the ensemble a sample is part of, or on whether a buffer is set
+ * (mclbm_forward_ckpt keeps single steps). mclbm_step_scratch_bytes gives the size (0 where no run of the
  * ensemble is large enough to gain): up to 2 GiB for samples of at most 64^3,
  * one sample's populations above. The closed-form stabiliser only; launch
  * timing (mclbm_time_launches) and mclbm_autotune take single steps.

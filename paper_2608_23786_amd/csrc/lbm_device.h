@@ -548,57 +548,143 @@ __device__ __forceinline__ NodeMoments<T> pair_moments(const T (&p)[Q]) {
   return m;
 }
 
+// Which of the two products u = j / rho in c_i.u of an edge (one zero component)
+// stays unrounded inside the sum, in the velocity-by-velocity collision below:
+// 0 x, 1 y, 2 z. A corner adds its z product to the sum of the edge (c_x, c_y, 0).
+template <int QN>
+__host__ __device__ constexpr int fused_axis(int i) {
+  const int a = cx(i), b = cy(i), c = cz(i);
+  if (c == 0) return b < 0 && (a < 0 || QN == 27) ? 0 : 1;
+  if (b == 0) return QN == 27 || (a < 0 && c < 0) ? 0 : 2;
+  return QN == 27 || (b < 0 && c < 0) ? 1 : 2;
+}
+
+// whether c_i.u and c_-i.u round to opposite numbers
+template <int QN>
+__host__ __device__ constexpr bool odd_velocity(int i) {
+  if (nonzeros(i) < 2) return true;
+  const int e = nonzeros(i) == 3 ? i - cz(i) : i;
+  return fused_axis<QN>(e) == fused_axis<QN>(26 - e);
+}
+
+template <int QN, int i>
+__device__ __forceinline__ float cdot_u(const Macro<float>& m) {
+  constexpr int a = cx(i), b = cy(i), c = cz(i);
+  if constexpr (nonzeros(i) < 2) {
+    return cdot<i>(m.ux, m.uy, m.uz);
+  } else if constexpr (nonzeros(i) == 3) {
+    return vfma(signed_term<c>(m.jz), m.inv, cdot_u<QN, i - c>(m));
+  } else if constexpr (fused_axis<QN>(i) == 0) {
+    return vfma(signed_term<a>(m.jx), m.inv, c == 0 ? signed_term<b>(m.uy) : signed_term<c>(m.uz));
+  } else if constexpr (fused_axis<QN>(i) == 1) {
+    return vfma(signed_term<b>(m.jy), m.inv, c == 0 ? signed_term<a>(m.ux) : signed_term<c>(m.uz));
+  } else {
+    return vfma(signed_term<c>(m.jz), m.inv, b == 0 ? signed_term<a>(m.ux) : signed_term<b>(m.uy));
+  }
+}
+
 // KBC collision of one node in place, g <- g*, velocity by velocity, with the
-// closed form. Between the passes g[] holds the shifted equilibrium, so every
-// g^eq_i is evaluated once.
-template <int QN, typename T>
-__device__ __forceinline__ CellResult<T> kbc_collide_each(T (&g)[Q], const Relax<T>& rp) {
-  CellResult<T> res;
+// closed form, in float: the collision of every FP32 kernel, of one step or of
+// two, so that a sample's populations are the same bits however its steps are
+// cut into calls, records and passes and whatever ensemble it is part of. Every
+// rounding is spelled out, as the compiler once chose it for the formulas at the
+// top of this file (which product of c.u stays unrounded included): results
+// have always been these. What is the same for +c and -c is formed once.
+// Between the passes g[] holds the shifted equilibrium.
+template <int QN>
+__device__ __forceinline__ CellResult<float> kbc_collide_each(float (&g)[Q], const Relax<float>& rp) {
+#pragma clang fp contract(off)
+  CellResult<float> res;
   res.m = macroscopic<QN>(g);
-  const Macro<T>& m = res.m;
-  T fneq[Q];
-  for_vel<QN>([&](auto ic) {
-    constexpr int i = decltype(ic)::value;
-    const T ge = geq<QN, i>(m);
+  Macro<float>& m = res.m;
+  m.usq15 = 1.5f * vfma(m.uz, m.uz, vfma(m.ux, m.ux, m.uy * m.uy));
+  constexpr float sixth = 1.0f / 6.0f, w13 = float(weight<QN>(13));
+  float fneq[Q];
+  // g^eq_i = w_i x_i + odd_i, x_i = drho + rho (4.5 (c_i.u)^2 - 1.5 |u|^2)
+  const float x13 = vfma(-m.rho, m.usq15, m.drho);
+  fneq[13] = vfma(-w13, x13, g[13]);
+  g[13] = w13 * x13;
+  for_pair<QN>([&](auto ic) {
+    constexpr int i = decltype(ic)::value, k = 26 - i;
+    constexpr float w = float(weight<QN>(i));
+    // 3 w_i c_i.j with 3 w_i split into a float head and tail: with the
+    // rounded weights alone, sum_i 3 w_i c_i c_i = (1 + 7.5e-9) I, a
+    // systematic momentum gain in every collision that accumulates over
+    // thousands of steps; with the tail the first moment of g^eq is j up
+    // to unbiased rounding.
+    constexpr float w3 = float(3.0 * weight<QN>(i)), w3_tail = float(3.0 * weight<QN>(i) - double(w3));
+    const float cj = cdot<i>(m.jx, m.jy, m.jz);
+    const float odd = vfma(w3, cj, w3_tail * cj);
+    auto even = [&](float cu) { return vfma(m.rho, vfma(4.5f * cu, cu, -m.usq15), m.drho); };
+    const float x = even(cdot_u<QN, i>(m));
+    float y = x;
+    if constexpr (!odd_velocity<QN>(i)) y = even(cdot_u<QN, k>(m));
+    const float ge = vfma(w, x, odd), gk = vfma(w, y, -odd);
     fneq[i] = g[i] - ge;
+    fneq[k] = g[k] - gk;
     g[i] = ge;
+    g[k] = gk;
   });
-  const Shear<T> s = shear_coefficients<QN>(fneq);
-  T A = T(0), B = T(0), fmin = T(1);
+  // second moments of f^neq and the shear part, faces without their 1 / 6
+  float pxx = 0.0f, pyy = 0.0f, pzz = 0.0f, pxy = 0.0f, pxz = 0.0f, pyz = 0.0f;
   for_vel<QN>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
-    const T feq = T(weight<QN>(i)) + g[i];
-    const T r = recip(feq);
-    fmin = vmin(fmin, feq);
-    if constexpr (nonzeros(i) == 1 || nonzeros(i) == 2) {
-      const T ds = shear_part<i>(s);
-      const T dh = fneq[i] - ds;
-      A += ds * dh * r;
-      B += dh * dh * r;
-    } else {
-      B += fneq[i] * fneq[i] * r;
-    }
+    if constexpr (cx(i) != 0) pxx += fneq[i];
+    if constexpr (cy(i) != 0) pyy += fneq[i];
+    if constexpr (cz(i) != 0) pzz += fneq[i];
+    if constexpr (cx(i) * cy(i) != 0) pxy += signed_term<cx(i) * cy(i)>(fneq[i]);
+    if constexpr (cx(i) * cz(i) != 0) pxz += signed_term<cx(i) * cz(i)>(fneq[i]);
+    if constexpr (cy(i) * cz(i) != 0) pyz += signed_term<cy(i) * cz(i)>(fneq[i]);
   });
-  const bool resolved = B > equilibrium_threshold<T>(m);
-  T gamma = T(2);
-  if (resolved) gamma = rp.two_over_omega - rp.kappa * (A / B);
-  T t = T(0.5) * rp.omega * gamma;
+  const float nxz = pxx - pzz, nyz = pyy - pzz;
+  const float sx = vfma(2.0f, nxz, -nyz), sy = vfma(2.0f, nyz, -nxz);
+  Shear<float> s;
+  s.dsx = sx * sixth;
+  s.dsy = sy * sixth;
+  s.dsz = -vfma(sx, sixth, s.dsy);
+  s.exy = 0.25f * pxy;
+  s.exz = 0.25f * pxz;
+  s.eyz = 0.25f * pyz;
+  float A = 0.0f, B = 0.0f, low = 1.0f;
+  for_vel<QN>([&](auto ic) {
+    constexpr int i = decltype(ic)::value;
+    const float feq = i == 13 ? vfma(w13, x13, w13) : float(weight<QN>(i)) + g[i];
+    const float r = recip(feq);
+    low = hwmin(low, feq);
+    float dh = fneq[i];
+    if constexpr (nonzeros(i) == 1 || nonzeros(i) == 2) {
+      if constexpr (nonzeros(i) == 1 && cx(i) != 0) dh = vfma(-sixth, sx, dh);
+      else if constexpr (nonzeros(i) == 1 && cy(i) != 0) dh = vfma(-sixth, sy, dh);
+      else dh = dh - shear_part<i>(s);
+      A = vfma(shear_part<i>(s) * dh, r, A);
+      fneq[i] = dh;
+    }
+    B = vfma(dh * dh, r, B);
+  });
+  // The sums are complete here: A, needed only where B is above its threshold,
+  // would otherwise be formed inside that branch, with the 45 values it is formed
+  // from kept until then (34-118 registers spilled in the two-step kernel).
+  asm volatile("" : "+v"(A), "+v"(B), "+v"(low));
+  const float least = fmaxf(1e-30f, 0x1.0p-40f * vfma(m.drho, m.drho, m.usq15 + m.usq15));  // equilibrium_threshold
+  float gamma = 2.0f;
+  if (B > least) gamma = vfma(-rp.kappa, A / B, rp.two_over_omega);
   // g* = g - omega ds - t dh = (g^eq - ds) + (2 - omega) ds + (1 - t) dh.
   // The shear relaxation enters through eps = 2 - omega, which keeps the
   // viscosity (proportional to eps for omega near 2) at full relative
   // precision even in float.
-  const T one_t = T(1) - t;
+  const float one_t = vfma(-0.5f * rp.omega, gamma, 1.0f);
   for_vel<QN>([&](auto ic) {
     constexpr int i = decltype(ic)::value;
     if constexpr (nonzeros(i) == 1 || nonzeros(i) == 2) {
-      const T ds = shear_part<i>(s);
-      g[i] = (g[i] - ds) + rp.eps * ds + one_t * (fneq[i] - ds);
+      const float ds = shear_part<i>(s);
+      g[i] = vfma(one_t, fneq[i], vfma(rp.eps, ds, g[i] - ds));
     } else {
-      g[i] = g[i] + one_t * fneq[i];
+      g[i] = vfma(one_t, fneq[i], g[i]);
     }
   });
   res.gamma = gamma;
-  res.bad = !(m.rho > T(0)) || !(m.usq15 < T(1.5)) || !(fmin > T(0));
+  // (a NaN drops out of the minimum and shows in the density or the velocity)
+  res.bad = !(m.rho > 0.0f) || !(m.usq15 < 1.5f) || !(low > 0.0f);
   return res;
 }
 
@@ -615,9 +701,11 @@ __device__ __forceinline__ CellResult<T> kbc_collide_each(T (&g)[Q], const Relax
 // The shear moments are those of g minus those of g^eq, which are rho u u
 // exactly (plus a trace that drops out of the differences). Every pair then
 // takes its new sum s - 2 omega ds - t sh and difference d - t dn. That is 14
-// reciprocals instead of 27 and half the sums: D3Q27 in float takes 490 vector
-// instructions and 16 reciprocals against 900 and 29 velocity by velocity, in
-// double 580 against 1130.
+// reciprocals instead of 27 and half the sums: D3Q27 in double takes 580 vector
+// instructions against 1130 velocity by velocity. (In float with the closed form
+// it would take 490 against 605, but round otherwise than the results have always
+// been; the passes of two steps, which are bound by arithmetic, took 3 to 4 % less
+// with it.)
 // In float 6 w is split into head and tail for dn: with the rounded weights
 // alone sum_i 3 w_i c_i c_i = (1 + 7.5e-9) I, a systematic momentum gain in
 // every collision that accumulates over thousands of steps. The shear
@@ -754,12 +842,10 @@ __device__ __forceinline__ CellResult<T> kbc_collide_pairs(T (&g)[Q], const Rela
   return res;
 }
 
-// The collision of the single-step kernels. Bound by memory in float with the
-// closed form, they keep the velocity-by-velocity form, whose results ensembles
-// of every size have always had; in double, whose divisions cost ten
-// instructions each (one 32^3 sample 8.7 -> 7.8 us a step, 11 x 64^3 215 -> 205),
-// and with the exact stabiliser, bound by arithmetic, the pairs are faster. The
-// two forms agree to rounding (float: 2e-8 of max |f - w| after 13 steps).
+// The collision of the kernels, of one step and of two alike: in float with the
+// closed form velocity by velocity (see there); in double, whose divisions cost
+// ten instructions each (one 32^3 sample 8.7 -> 7.8 us a step, 11 x 64^3 215 ->
+// 205), and with the exact stabiliser, bound by arithmetic, over pairs.
 template <int QN, bool EXACT = false, typename T>
 __device__ __forceinline__ CellResult<T> kbc_collide(T (&g)[Q], const Relax<T>& rp) {
   if constexpr (std::is_same<T, float>::value && !EXACT) return kbc_collide_each<QN>(g, rp);

@@ -270,7 +270,7 @@ __global__ void __launch_bounds__((R + SIDE) * LX) kbc_step2_kernel(Step2Args<T>
     // first collision of a plane; its values to LDS and, shifted along x, to now
     auto first_collision = [&]() {
       __builtin_amdgcn_sched_barrier(0);
-      const CellResult<T> res = kbc_collide_pairs<QN, false>(g, rp);
+      const CellResult<T> res = kbc_collide<QN>(g, rp);
       __builtin_amdgcn_sched_barrier(0);
       bad = bad || res.bad;
       int col, row;
@@ -381,7 +381,7 @@ __global__ void __launch_bounds__((R + SIDE) * LX) kbc_step2_kernel(Step2Args<T>
         release();
         if (zz < z1) load_plane(zz + 1);
         __builtin_amdgcn_sched_barrier(0);
-        const CellResult<T> res = kbc_collide_pairs<QN, false>(f, rp);
+        const CellResult<T> res = kbc_collide<QN>(f, rp);
         __builtin_amdgcn_sched_barrier(0);
         int col, row;
         row_thread(col, row);

@@ -116,8 +116,8 @@ class Ensemble:
 
     def two_step(self, enable: bool) -> bool:
         """Give the library the scratch buffer with which steps between records
-        take two steps per pass over memory (the same results, bit for bit in
-        FP64 and to rounding in FP32), or take it back. Ensembles too small to gain need none, and where the buffer
+        take two steps per pass over memory (the same populations, bit for bit),
+        or take it back. Ensembles too small to gain need none, and where the buffer
         does not fit, or one of more than 4 GiB would take over a quarter of the
         free device memory, the ensemble keeps single steps. Returns whether a
         buffer is set."""
