@@ -44,7 +44,7 @@ int ilog2(int v) {
 }
 bool is_pow2(int64_t v) { return v > 0 && (v & (v - 1)) == 0; }
 
-constexpr int kMinBlock = 128;        // smallest collide-and-stream block, which small launches take
+constexpr int kMinBlock = kSmallBlock;  // smallest collide-and-stream block, which small launches take
 constexpr int64_t kSmallNodes = 1 << 18;
 constexpr int kAuxBlock = 256;        // block of the auxiliary kernels
 constexpr int kMaxTables = 128;       // launch tables kept in the workspace
@@ -92,7 +92,7 @@ struct Table {
   int block = 0;
   int total_blocks = 0;
   int most_blocks = 0;       // of one segment
-  UniformSegs uniform{};     // the table as kernel arguments, where its segments allow it
+  UniformSegs uniform{};     // the table as kernel arguments: small launches whose segments allow it
   std::vector<Seg> host;     // persistent host copy (source of the upload)
 };
 
@@ -353,7 +353,7 @@ mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool par
   t.block = block;
   t.total_blocks = first;
   for (const Seg& g : segs) t.most_blocks = std::max(t.most_blocks, int(g.nblocks));
-  t.uniform = uniform_segs(c, segs);
+  if (block == kSmallBlock && int64_t(first) * block < kSmallNodes) t.uniform = uniform_segs(c, segs);
   t.host = segs;
   c->table_next += slot;
   if (!segs.empty()) {

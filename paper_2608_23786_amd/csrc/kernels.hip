@@ -305,11 +305,12 @@ __global__ void __launch_bounds__(256) adjoint_seed_kernel(const T* pop, T* lam,
 // f*_i = w_i + g_i - omega ds_i - t dh_i; by the implicit function theorem
 // dt = (dF at fixed t) / D, D = sum_i dh_i^2 / f*_i, so the adjoint of t
 // reaches F's inputs (dh, ds and g directly) with weight tbar / D.
-template <int QN, typename T, int BLOCK, bool BUF, bool EXACT>
+// ARGS: the launch table comes as kernel arguments, as in the step kernels.
+template <int QN, typename T, int BLOCK, bool BUF, bool EXACT, bool ARGS>
 __global__ void __launch_bounds__(BLOCK) adjoint_step_kernel(const T* state, const T* lam_in, T* lam_out,
                                                            const DevSample* samples, const Seg* segs,
                                                            UniformSegs uniform, int nseg) {
-  const BlockSite site = block_site(uniform, segs, nseg, samples, blockIdx.x);
+  const BlockSite site = ARGS ? block_site(uniform, blockIdx.x) : block_site(segs, nseg, samples, blockIdx.x);
   const int l = site.log2n;
   const Cell c = make_cell(site.local_block * uint32_t(BLOCK) + threadIdx.x, l);
   const Relax<T> rp = relax_of<T>(samples[site.sample]);
@@ -896,7 +897,7 @@ hipError_t launch_adjoint_seed(int q, int precision, const void* pop, void* lam,
 }
 
 namespace {
-template <int QN, typename T, int BLOCK>
+template <int QN, typename T, int BLOCK, bool ARGS>
 hipError_t launch_adjoint_step_t(const T* a, const T* b, T* o, const DevSample* samples, const Seg* segs,
                                  const UniformSegs& uniform, int32_t nseg, int32_t total_blocks, int32_t buffer_ok,
                                  int32_t exact_gamma, hipStream_t s) {
@@ -905,17 +906,17 @@ hipError_t launch_adjoint_step_t(const T* a, const T* b, T* o, const DevSample* 
     // FP64 only (the host refuses FP32): see mclbm_backward
     if constexpr (!std::is_same<T, double>::value) return hipErrorInvalidValue;
     else if (buffer_ok)
-      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, true>), grid, blk, 0, s, a, b, o, samples, segs,
-                         uniform, nseg);
+      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, true, ARGS>), grid, blk, 0, s, a, b, o, samples,
+                         segs, uniform, nseg);
     else
-      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, true>), grid, blk, 0, s, a, b, o, samples, segs,
-                         uniform, nseg);
+      hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, true, ARGS>), grid, blk, 0, s, a, b, o, samples,
+                         segs, uniform, nseg);
   } else if (buffer_ok) {
-    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, false>), grid, blk, 0, s, a, b, o, samples, segs,
+    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, true, false, ARGS>), grid, blk, 0, s, a, b, o, samples, segs,
                        uniform, nseg);
   } else {
-    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, false>), grid, blk, 0, s, a, b, o, samples, segs,
-                       uniform, nseg);
+    hipLaunchKernelGGL((adjoint_step_kernel<QN, T, BLOCK, false, false, ARGS>), grid, blk, 0, s, a, b, o, samples,
+                       segs, uniform, nseg);
   }
   return hipGetLastError();
 }
@@ -931,12 +932,15 @@ hipError_t launch_adjoint_step(int q, int precision, const void* state, const vo
     const T* a = static_cast<const T*>(state);
     const T* b = static_cast<const T*>(lam_in);
     T* o = static_cast<T*>(lam_out);
-    if (block == 128)
-      return launch_adjoint_step_t<QN, T, 128>(a, b, o, samples, segs, uniform, nseg, total_blocks, buffer_ok,
-                                               exact_gamma, s);
+    if (block == kSmallBlock && uniform.on)
+      return launch_adjoint_step_t<QN, T, kSmallBlock, true>(a, b, o, samples, segs, uniform, nseg, total_blocks,
+                                                             buffer_ok, exact_gamma, s);
+    if (block == kSmallBlock)
+      return launch_adjoint_step_t<QN, T, kSmallBlock, false>(a, b, o, samples, segs, uniform, nseg, total_blocks,
+                                                              buffer_ok, exact_gamma, s);
     if (block == 256)
-      return launch_adjoint_step_t<QN, T, 256>(a, b, o, samples, segs, uniform, nseg, total_blocks, buffer_ok,
-                                               exact_gamma, s);
+      return launch_adjoint_step_t<QN, T, 256, false>(a, b, o, samples, segs, uniform, nseg, total_blocks, buffer_ok,
+                                                      exact_gamma, s);
     return hipErrorInvalidValue;
   });
 }

@@ -92,6 +92,8 @@ struct Seg {
   int32_t parity;         // steps taken so far, modulo 2 (AA layout of the state)
 };
 
+constexpr int kSmallBlock = 128;  // threads per block of small launches, which take their table as arguments
+
 // A launch table whose segments are consecutive samples of one resolution and
 // parity, as kernel arguments: a block then finds its nodes without reading the
 // table and the sample first, two dependent loads that a small launch waits for.

@@ -1109,17 +1109,14 @@ struct BlockSite {
   uint32_t pstride;
   uint64_t offset;        // element offset of the sample's populations
 };
-__device__ __forceinline__ BlockSite block_site(const UniformSegs& u, const Seg* segs, int nseg,
-                                                const DevSample* samples, int b) {
-  if (u.on) {
-    const int s = b >> u.shift;
-    return {u.sample0 + s, u.log2n, u.parity, uint32_t(b - (s << u.shift)), u.pstride,
-            u.offset0 + uint64_t(s) * u.stride};
-  }
+__device__ __forceinline__ BlockSite block_site(const UniformSegs& u, int b) {
+  const int s = b >> u.shift;
+  return {u.sample0 + s, u.log2n, u.parity, uint32_t(b - (s << u.shift)), u.pstride, u.offset0 + uint64_t(s) * u.stride};
+}
+__device__ __forceinline__ BlockSite block_site(const Seg* segs, int nseg, const DevSample* samples, int b) {
   const Seg sg = segs[find_segment(segs, nseg, b)];
   const DevSample& sp = samples[sg.sample];
-  return {int32_t(uniform32(sg.sample)), int32_t(uniform32(sp.log2n)), int32_t(uniform32(sg.parity)),
-          uniform32(uint32_t(b - sg.first_block)), uniform32(sp.pstride), uniform64(sp.offset)};
+  return {sg.sample, sp.log2n, sg.parity, uint32_t(b - sg.first_block), sp.pstride, sp.offset};
 }
 
 __device__ __forceinline__ double wave_sum(double v) {

@@ -16,23 +16,43 @@ struct StepArgs {
   T* dst;
   const DevSample* samples;
   const Seg* segs;
-  UniformSegs uniform;
   int32_t nseg;
   int32_t total_blocks;
   int32_t xcd_remap;
   int32_t* flags;
   double* partials;
   double* vel;  // record ticks: the velocity of the state read, per sample at voffset (NULL: none)
+  UniformSegs uniform;  // the table, for ARGS
 };
 
-template <int QN, typename T, int BLOCK, StepKind KIND, bool BUF, bool NT, bool EXACT = false>
+// Large launches in float run at what the memory makes of 2 q streams, and it makes
+// less of them the closer together their accesses come. So the stores of a node
+// are issued 16 cycles apart, and launches of kCapNodes to kCapMost nodes are held
+// to three waves per SIMD by the LDS they ask for, which the kernel does not use.
+// us per step with the stores back to back / apart / apart and three waves:
+// 64 x 64^3 616 / 601 / 580, 8 x 128^3 645 / 638 / 616, one 256^3 659 / 644 / 626,
+// 1000 x 32^3 1228 / 1215 / 1163; D3Q19 421 / 419 / 406, 444 / 443 / 428, 450 / 446 /
+// 431, 821 / 832 / 820. On either side of the lines the waves help more than they
+// cost: 8 x 64^3 75.9 free, 77.0 held (16 x 64^3 149.8, 148.4); 512^3 5858, 6016.
+constexpr int64_t kCapNodes = 1 << 22, kCapMost = 1 << 26;
+constexpr unsigned cap_lds(int block) { return unsigned(160 * 1024 / (3 * 256 / block)) - 4096; }
+
+template <bool APART>
+__device__ __forceinline__ void between_stores() {
+  if constexpr (APART) asm volatile("s_nop 15");
+}
+
+// ARGS: the launch table comes as kernel arguments, which small launches wait
+// less for; large ones read it.
+template <int QN, typename T, int BLOCK, StepKind KIND, bool BUF, bool NT, bool EXACT = false, bool ARGS = false>
 __global__ void __launch_bounds__(BLOCK) kbc_step_kernel(StepArgs<T> a) {
   const int b = remap_block(blockIdx.x, a.total_blocks, a.xcd_remap);
-  const BlockSite site = block_site(a.uniform, a.segs, a.nseg, a.samples, b);
+  const BlockSite site = ARGS ? block_site(a.uniform, b) : block_site(a.segs, a.nseg, a.samples, b);
   const DevSample& sp = a.samples[site.sample];
   const int l = site.log2n;
   const Cell c = make_cell(site.local_block * BLOCK + threadIdx.x, l);
   using Planes = typename std::conditional<BUF, BufPlanes<T, NT, QN>, PtrPlanes<T, NT, QN>>::type;
+  constexpr bool APART = std::is_same<T, float>::value && !EXACT && !ARGS;
   const Planes src(a.pop + site.offset, site.pstride);
   const bool odd = (KIND != kPush) && (site.parity & 1);
 
@@ -84,18 +104,21 @@ __global__ void __launch_bounds__(BLOCK) kbc_step_kernel(StepArgs<T> a) {
         constexpr int i = decltype(ic)::value;
         const Slot s = aa_write_slot<i>(c, false);
         dst.store(s.vel, s.idx, g[i]);
+        between_stores<APART>();
       });
     } else if (rows) {
       row_shift<QN, +1, BLOCK>(g, edge_out, n);
       for_vel<QN>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         dst.store(i, neighbour_yz<i, +1>(c), g[i]);
+        between_stores<APART>();
       });
     } else {
       for_vel<QN>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         const Slot s = aa_write_slot<i>(c, true);
         dst.store(s.vel, s.idx, g[i]);
+        between_stores<APART>();
       });
     }
   }
@@ -128,15 +151,26 @@ hipError_t launch_step_t(const StepLaunch& L, hipStream_t s) {
   a.partials = L.partials;
   a.vel = L.vel;
   const dim3 grid(L.total_blocks), blk(BLOCK);
-  if (buf && L.nontemporal)
-    hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, true, true>), grid, blk, 0, s, a);
-  else if (buf)
-    hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, true, false>), grid, blk, 0, s, a);
-  else if (L.nontemporal)
-    hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, false, true>), grid, blk, 0, s, a);
-  else
-    hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, false, false>), grid, blk, 0, s, a);
-  return hipGetLastError();
+  const int64_t nodes = int64_t(L.total_blocks) * BLOCK;
+  const bool cap = std::is_same<T, float>::value && BLOCK <= 256 && KIND != kReduceOnly && nodes >= kCapNodes &&
+                   nodes <= kCapMost;
+  const unsigned lds = cap ? cap_lds(BLOCK) : 0;
+  auto launch = [&](auto args) {
+    constexpr bool ARGS = decltype(args)::value;
+    if (buf && L.nontemporal)
+      hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, true, true, false, ARGS>), grid, blk, lds, s, a);
+    else if (buf)
+      hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, true, false, false, ARGS>), grid, blk, lds, s, a);
+    else if (L.nontemporal)
+      hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, false, true, false, ARGS>), grid, blk, lds, s, a);
+    else
+      hipLaunchKernelGGL((kbc_step_kernel<QN, T, BLOCK, KIND, false, false, false, ARGS>), grid, blk, lds, s, a);
+    return hipGetLastError();
+  };
+  if constexpr (BLOCK == kSmallBlock) {
+    if (L.uniform.on) return launch(std::true_type{});
+  }
+  return launch(std::false_type{});
 }
 
 template <int QN, typename T, StepKind KIND>
