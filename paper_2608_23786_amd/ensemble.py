@@ -69,6 +69,10 @@ class Ensemble:
             nbytes = 256
         self.stream = stream if stream is not None else torch.cuda.Stream(device=self.device)
         self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
+        # the allocator may hand out memory that work queued on the caller's stream still uses:
+        # the library writes it on its own stream, and on the null stream while it sets up
+        torch.cuda.current_stream(self.device).synchronize()
+        self._consume(self.workspace)
         base = self.workspace.data_ptr()
         self._ws_ptr = (base + 255) // 256 * 256
         self._ctx = ctypes.c_void_p()
@@ -133,6 +137,7 @@ class Ensemble:
             except torch.cuda.OutOfMemoryError:
                 pass
         if scratch is not None:
+            self._consume(scratch)
             base = (scratch.data_ptr() + 255) // 256 * 256
             check(lib().mclbm_set_step_scratch(self._ctx, ctypes.c_void_p(base), nb))
         elif self._scratch is not None:
