@@ -59,6 +59,7 @@ class Ensemble:
         self.samples: List[Sample] = list(samples)
         self.m = len(self.samples)
         self.precision = precision
+        self._least_stride = min((max(1, s.stride) for s in self.samples), default=1)
         self.q = int(lattice)   # 27 (D3Q27) or 19 (D3Q19); the library validates it
         self.device = torch.device(device)
         L = lib()
@@ -79,7 +80,10 @@ class Ensemble:
         check(L.mclbm_create(ctypes.byref(self._ctx), self.m, self._desc, PRECISIONS[precision], self.q,
                              ctypes.c_void_p(self._ws_ptr), nbytes, ctypes.c_void_p(self.stream.cuda_stream)))
         self._scratch = None
-        self.two_step(True)
+        self._scratch_need = int(L.mclbm_step_scratch_bytes(self._ctx))
+        self._two_step = True     # the first step that can use the scratch buffer takes it
+        self._captured = False    # a step was captured: what it uses stays
+        self._exact = False
 
     def __del__(self):
         ctx = getattr(self, "_ctx", None)
@@ -92,6 +96,13 @@ class Ensemble:
 
     # ------------------------------------------------------------ helpers
     def _dev_empty(self, shape, dtype=torch.float64):
+        with torch.cuda.stream(self.stream):
+            try:
+                return torch.empty(shape, dtype=dtype, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                if self._scratch is None or self._captured:
+                    raise
+        self.two_step(False)
         with torch.cuda.stream(self.stream):
             return torch.empty(shape, dtype=dtype, device=self.device)
 
@@ -121,29 +132,38 @@ class Ensemble:
     def two_step(self, enable: bool) -> bool:
         """Give the library the scratch buffer with which steps between records
         take two steps per pass over memory (the same populations, bit for bit),
-        or take it back. Ensembles too small to gain need none, and where the buffer
-        does not fit, or one of more than 4 GiB would take over a quarter of the
-        free device memory, the ensemble keeps single steps. Returns whether a
-        buffer is set."""
-        if enable and self._scratch is not None:
-            return True
-        nb = int(lib().mclbm_step_scratch_bytes(self._ctx)) if enable else 0
-        if nb > 4 << 30 and nb > torch.cuda.mem_get_info(self.device)[0] // 4:
-            nb = 0
-        scratch = None
-        if nb:
-            try:
-                scratch = torch.empty(nb + 256, dtype=torch.uint8, device=self.device)
-            except torch.cuda.OutOfMemoryError:
-                pass
-        if scratch is not None:
-            self._consume(scratch)
-            base = (scratch.data_ptr() + 255) // 256 * 256
-            check(lib().mclbm_set_step_scratch(self._ctx, ctypes.c_void_p(base), nb))
+        or take it back. By default the first step() that can use a buffer takes
+        one, of up to 2 GiB (above 64^3 the size of one sample's populations);
+        ensembles too small to gain, or with the exact stabiliser, need none, and
+        where it would take over a quarter of the free device memory the ensemble
+        keeps single steps. It is given back when a later call of this ensemble
+        runs out of device memory, or with two_step(False), after which no step
+        takes one. Returns whether a buffer is set."""
+        if enable:
+            self._take_scratch()
         elif self._scratch is not None:
             check(lib().mclbm_set_step_scratch(self._ctx, None, 0))
+            self._scratch = None
+        self._two_step = False
+        return self._scratch is not None
+
+    def _take_scratch(self):
+        nb = self._scratch_need
+        if nb == 0 or self._scratch is not None:
+            return
+        # blocks that the allocator holds but nobody uses are free as well
+        free = torch.cuda.mem_get_info(self.device)[0]
+        free += torch.cuda.memory_reserved(self.device) - torch.cuda.memory_allocated(self.device)
+        if nb > free // 4:
+            return
+        try:
+            scratch = torch.empty(nb + 256, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            return
+        self._consume(scratch)
+        base = (scratch.data_ptr() + 255) // 256 * 256
+        check(lib().mclbm_set_step_scratch(self._ctx, ctypes.c_void_p(base), nb))
         self._scratch = scratch
-        return scratch is not None
 
     # ------------------------------------------------------------ lifecycle
     def init(self, seed: int = 0, y: Optional[torch.Tensor] = None):
@@ -165,6 +185,12 @@ class Ensemble:
         check(lib().mclbm_set_viscosity(self._ctx, arr))
 
     def step(self, ticks: int, record_every: int = 0) -> Optional[torch.Tensor]:
+        if self._scratch_need and torch.cuda.is_current_stream_capturing():
+            self._captured = True
+        elif self._scratch_need and self._two_step and not self._exact:
+            plain = ticks if record_every <= 0 else min(record_every - 1, ticks)   # ticks between records
+            if plain // self._least_stride >= 4:
+                self.two_step(True)
         if record_every > 0:
             nrec = (ticks + record_every - 1) // record_every
             rec = self._dev_empty((max(nrec, 1), self.m, 8))
@@ -420,6 +446,7 @@ class Ensemble:
         if mode not in modes:
             raise ValueError(f"stabiliser must be one of {list(modes)}")
         check(lib().mclbm_set_stabiliser(self._ctx, modes[mode]))
+        self._exact = mode == "exact"
 
     def use_graphs(self, enable: bool):
         check(lib().mclbm_use_graphs(self._ctx, int(enable)))
