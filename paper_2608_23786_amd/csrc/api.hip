@@ -53,7 +53,7 @@ constexpr uint64_t kCkptMagic = 0x4d434c424d434b50ull;
 constexpr size_t kFwdHeaderBytes = 256;  // forward checkpoints: the token of the forward that wrote them
 std::atomic<uint64_t> g_fwd_tokens{0};
 constexpr size_t kMaxRuns = 16;       // two-step passes: runs of equal resolution in an ensemble
-// Nodes of a run from which a pass of two steps is the faster way.
+// Nodes of a run from which a pass of two steps may be the faster way.
 constexpr int64_t kTwoStepNodes = 1 << 20;
 constexpr int kMaxObservablesN = 512;  // the FFT passes are instantiated for n = 8..512
 
@@ -161,9 +161,9 @@ struct mclbm_ctx {
   std::map<std::string, Table> tables;
   size_t table_next = 0;
 
-  // graphs keyed by the tick phase
+  // graphs keyed by the tick phase and the runs they leave out
   bool use_graphs = true;
-  std::map<int64_t, hipGraphExec_t> graphs;
+  std::map<std::pair<int64_t, uint32_t>, hipGraphExec_t> graphs;
   int64_t graph_ticks = 0;
 
   // launch timing
@@ -450,9 +450,10 @@ int64_t graph_length(const mclbm_ctx* c) {
 // them stay resident in the table pool while the graph exists.
 bool graphs_possible(const mclbm_ctx* c) { return 2 * int64_t(c->max_stride) <= kMaxTables / 4; }
 
-mclbm_status run_graph(mclbm_ctx* c) {
+// `among` as in run_tick; `without` names the same samples: a bit for every run that is not among them.
+mclbm_status run_graph(mclbm_ctx* c, const std::vector<char>* among, uint32_t without) {
   const int64_t len = graph_length(c);
-  const int64_t phase = c->tick % (2 * int64_t(c->max_stride));
+  const auto phase = std::make_pair(c->tick % (2 * int64_t(c->max_stride)), without);
   auto it = c->graphs.find(phase);
   if (it == c->graphs.end()) {
     // leave room for every table of the period so that none is evicted
@@ -465,7 +466,7 @@ mclbm_status run_graph(mclbm_ctx* c) {
     std::vector<int64_t> steps0 = c->steps;
     for (int64_t k = 0; k < len; ++k) {
       const Table* t = nullptr;
-      mclbm_status st = get_table(c, c->tick, false, step_block(c, c->tick, false), false, &t);
+      mclbm_status st = get_table(c, c->tick, false, step_block(c, c->tick, false, among), false, &t, among);
       if (st != MCLBM_OK) return st;
       for (const Seg& g : t->host) c->steps[g.sample] += 1;
       c->tick += 1;
@@ -474,7 +475,7 @@ mclbm_status run_graph(mclbm_ctx* c) {
     c->steps = steps0;
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     mclbm_status st = MCLBM_OK;
-    for (int64_t k = 0; k < len && st == MCLBM_OK; ++k) st = run_tick(c, nullptr);
+    for (int64_t k = 0; k < len && st == MCLBM_OK; ++k) st = run_tick(c, nullptr, among);
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamEndCapture(c->stream, &graph);
     c->tick = tick0;
@@ -494,22 +495,23 @@ mclbm_status run_graph(mclbm_ctx* c) {
   // bookkeeping of the ticks the graph ran
   for (int64_t k = 0; k < len; ++k) {
     for (int s = 0; s < c->m; ++s)
-      if (c->tick % c->desc[s].stride == 0) c->steps[s] += 1;
+      if (c->tick % c->desc[s].stride == 0 && (!among || (*among)[s])) c->steps[s] += 1;
     c->tick += 1;
   }
   return MCLBM_OK;
 }
 
-mclbm_status run_tick_loop(mclbm_ctx* c, int64_t ticks) {
+mclbm_status run_tick_loop(mclbm_ctx* c, int64_t ticks, const std::vector<char>* among = nullptr,
+                           uint32_t without = 0) {
   int64_t left = ticks;
   const int64_t len = graph_length(c);
   while (left > 0) {
     if (c->use_graphs && c->stream && !c->timing && graphs_possible(c) && left >= len) {
-      mclbm_status st = run_graph(c);
+      mclbm_status st = run_graph(c, among, without);
       if (st != MCLBM_OK) return st;
       left -= len;
     } else {
-      mclbm_status st = run_tick(c, nullptr);
+      mclbm_status st = run_tick(c, nullptr, among);
       if (st != MCLBM_OK) return st;
       left -= 1;
     }
@@ -541,16 +543,35 @@ int run_chunk(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   return (r.count + trips - 1) / trips;
 }
 
-// Whether passes of two pay for a run (us per tick of single steps / passes at
-// 2^20 nodes: 32^3 FP32 39.8 / 35.7, D3Q19 27.9 / 26.8; 64^3 40.1 / 36.2, 28.1 /
-// 26.7; FP64 1.13-1.38 x; at 2^24 1.12-1.57 x throughout). Not 32^3 of D3Q27 in
-// FP64, whose tile of two rows per wave does not fit the registers (62 spilled):
-// 77.5 / 105 at 2^20, 1229 / 1467 at 2^24.
+int64_t nodes_of(const mclbm_ctx* c, const mclbm_ctx::Run& r) { return int64_t(r.count) * c->cells(r.first); }
+
+// Whether a run is large enough for passes of two. Not 32^3 of D3Q27 in FP64,
+// whose tile of two rows per wave does not fit the registers (62 spilled; us per
+// tick of single steps / passes 77.5 / 105 at 2^20 nodes, 1229 / 1467 at 2^24).
 bool two_step_size(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   const int n = c->desc[r.first].n;
   if (n == 32 && c->q == 27 && c->precision == 0) return false;
-  return n <= 512 && int64_t(r.count) * n * n * n >= kTwoStepNodes;
+  return n <= 512 && nodes_of(c, r) >= kTwoStepNodes;
 }
+
+// Whether passes pay for a run by itself (us per tick of single steps / passes,
+// FP32, at 2^20 nodes: 8^3 38.5 / 31.0, D3Q19 26.6 / 23.0; 32^3 38.9 / 36.7; 64^3
+// 38.7 / 36.8; at 2^21 74.8 / 60.4, 76.4 / 64.2, 52.2 / 44.2, 53.1 / 46.9; at 2^24
+// 1.15-1.6 x throughout; FP64 1.1-1.4 x from 2^20 on). On D3Q19 in FP32 from 32^3
+// they do from 5 x 2^18 nodes on (2^20: 26.9 / 27.4, 26.7 / 27.2; here 34.7 / 32.7,
+// 34.1 / 32.0).
+bool two_step_pays(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
+  if (!two_step_size(c, r)) return false;
+  const bool close = c->precision != 0 && c->q == 19 && c->desc[r.first].n >= 32;
+  return !close || nodes_of(c, r) >= kTwoStepNodes * 5 / 4;
+}
+
+// In FP32 samples that step beside the runs in passes need launches of their own
+// then, about 4 us a tick, which runs of fewer nodes do not win back (us per tick
+// together / apart, 64^3 samples beside small ones: four 39.9 / 41.1, D3Q19 27.9 /
+// 30.7; five 50.0 / 48.5, 34.9 / 35.5; one 128^3 beside three 64^3 107.1 / 98.1,
+// 74.4 / 71.5). In FP64 1.06-1.25 x from 2^20 on.
+constexpr int64_t kBesideNodes = 1 << 21;
 
 // Whether a run is one step from the parity its passes start from.
 bool parity_off(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
@@ -644,30 +665,30 @@ mclbm_status run_plain_ticks(mclbm_ctx* c, int64_t ticks) {
       const int64_t steps = (c->tick + ticks + stride - 1) / stride - (c->tick + stride - 1) / stride;
       bool same = true;
       for (int s = r.first + 1; s < r.first + r.count; ++s) same = same && !((c->steps[s] ^ c->steps[r.first]) & 1);
-      if (same && two_step_size(c, r) && steps - parity_off(c, r) >= 4 &&
+      if (same && two_step_pays(c, r) && steps - parity_off(c, r) >= 4 &&
           state_bytes_of(c, r.first) * size_t(run_chunk(c, r)) <= c->scratch_bytes)
         two.push_back({&r, steps});
     }
   }
+  int64_t others = c->m, nodes = 0;
+  for (const auto& t : two) {
+    others -= t.first->count;
+    nodes += nodes_of(c, *t.first);
+  }
+  if (others > 0 && c->precision != 0 && nodes < kBesideNodes) two.clear();
   if (two.empty()) return run_tick_loop(c, ticks);
-  int64_t others = c->m;
+  uint32_t without = 0;
   rest.assign(size_t(c->m), 1);
   for (const auto& t : two) {
     std::fill(rest.begin() + t.first->first, rest.begin() + t.first->first + t.first->count, 0);
-    others -= t.first->count;
+    without |= 1u << (t.first - c->runs.data());
   }
   for (const auto& t : two) {
     const mclbm_status st = run_steps_two(c, *t.first, t.second);
     if (st != MCLBM_OK) return st;
   }
-  if (others == 0) {
-    c->tick += ticks;
-    return MCLBM_OK;
-  }
-  for (int64_t k = 0; k < ticks; ++k) {
-    const mclbm_status st = run_tick(c, nullptr, &rest);
-    if (st != MCLBM_OK) return st;
-  }
+  if (others > 0) return run_tick_loop(c, ticks, &rest, without);
+  c->tick += ticks;
   return MCLBM_OK;
 }
 
