@@ -91,7 +91,7 @@ struct Table {
   int nseg = 0;
   int block = 0;
   int total_blocks = 0;
-  int most_blocks = 0;       // of one segment
+  int most_blocks = 0, least_blocks = 0;  // of one segment
   UniformSegs uniform{};     // the table as kernel arguments: small launches whose segments allow it
   std::vector<Seg> host;     // persistent host copy (source of the upload)
 };
@@ -352,7 +352,10 @@ mclbm_status get_table(mclbm_ctx* c, int64_t tick, bool all, int block, bool par
   t.nseg = int(segs.size());
   t.block = block;
   t.total_blocks = first;
-  for (const Seg& g : segs) t.most_blocks = std::max(t.most_blocks, int(g.nblocks));
+  for (const Seg& g : segs) {
+    t.most_blocks = std::max(t.most_blocks, int(g.nblocks));
+    t.least_blocks = t.least_blocks ? std::min(t.least_blocks, int(g.nblocks)) : int(g.nblocks);
+  }
   if (block == kSmallBlock && int64_t(first) * block < kSmallNodes) t.uniform = uniform_segs(c, segs);
   t.host = segs;
   c->table_next += slot;
@@ -432,7 +435,7 @@ mclbm_status run_tick(mclbm_ctx* c, double* record_out, const std::vector<char>*
     HIP_TRY(launch_step(c->q, c->precision, record_out ? kStepRecord : kStep, L, c->stream));
     if (c->timing) HIP_TRY(hipEventRecord(e1, c->stream));
     if (record_out)
-      HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, record_out, c->stream));
+      HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->total_blocks, t->most_blocks, c->d_samples, record_out, c->stream));
     for (const Seg& g : t->host) c->steps[g.sample] += 1;
   }
   c->tick += 1;
@@ -875,7 +878,7 @@ mclbm_status mclbm_init(mclbm_ctx* c, uint64_t seed, const double* y_host) {
   st = get_table(c, 0, true, kAuxBlock, true, &t);
   if (st != MCLBM_OK) return st;
   c->generation += 1;
-  HIP_TRY(launch_init(c->q, c->precision, c->pop, c->d_samples, table_ptr(c, t), t->nseg, t->total_blocks, t->most_blocks, c->d_ycoef,
+  HIP_TRY(launch_init(c->q, c->precision, c->pop, c->d_samples, table_ptr(c, t), t->nseg, t->total_blocks, t->least_blocks, c->d_ycoef,
                       c->stream));
   c->initialized = true;
   return MCLBM_OK;
@@ -954,7 +957,7 @@ mclbm_status mclbm_reduce(mclbm_ctx* c, double* red_dev) {
   if (st != MCLBM_OK) return st;
   StepLaunch L = make_launch(c, t, c->pop, nullptr);
   HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
-  HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, red_dev, c->stream));
+  HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->total_blocks, t->most_blocks, c->d_samples, red_dev, c->stream));
   return check_flags(c, nullptr);
 }
 
@@ -1155,7 +1158,7 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
     if (st != MCLBM_OK) return st;
     StepLaunch L = make_launch(c, t, c->pop, nullptr);
     HIP_TRY(launch_step(c->q, c->precision, kReduceOnly, L, c->stream));
-    HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->most_blocks, c->d_samples, records, c->stream));
+    HIP_TRY(launch_record_finalize(c->d_partials, L.segs, t->nseg, t->total_blocks, t->most_blocks, c->d_samples, records, c->stream));
     HIP_TRY(launch_extract(records, c->m, 4, ke_dev, c->stream));
   }
 
@@ -1197,8 +1200,8 @@ mclbm_status mclbm_backward(mclbm_ctx* c, int64_t ticks, int32_t ckpt_every, con
     }
   }
   HIP_TRY(launch_init_adjoint(c->q, c->precision, lam[cur], c->d_samples, table_ptr(c, nat), nat->nseg, nat->total_blocks,
-                              nat->most_blocks, c->d_ycoef, partials, c->stream));
-  HIP_TRY(launch_init_adjoint_finalize(partials, table_ptr(c, nat), nat->nseg, nat->total_blocks, c->d_samples, c->d_pmat, dJdY_dev,
+                              nat->least_blocks, c->d_ycoef, partials, c->stream));
+  HIP_TRY(launch_init_adjoint_finalize(partials, table_ptr(c, nat), nat->nseg, nat->total_blocks, nat->least_blocks, c->d_samples, c->d_pmat, dJdY_dev,
                                        c->stream));
   return MCLBM_OK;
 }

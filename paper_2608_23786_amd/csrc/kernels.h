@@ -75,13 +75,13 @@ hipError_t launch_step2_d3q19_f32(const Step2Launch& L, hipStream_t s);
 hipError_t launch_step2_d3q19_f64(const Step2Launch& L, hipStream_t s);
 
 // Records from block partials (which are overwritten), writes out[sample*kRecord + k];
-// most_blocks: the largest nblocks of the segments.
-hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nseg, int32_t most_blocks,
-                                  const DevSample* samples, double* out, hipStream_t s);
+// most_blocks: the largest nblocks of the segments (least_blocks below: the smallest).
+hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nseg, int32_t total_blocks,
+                                  int32_t most_blocks, const DevSample* samples, double* out, hipStream_t s);
 
 // Initial equilibrium populations of every sample in `segs` (blocks of 256 cells).
 hipError_t launch_init(int q, int precision, void* pop, const DevSample* samples, const Seg* segs, int32_t nseg,
-                       int32_t total_blocks, int32_t most_blocks, const double* ycoef, hipStream_t s);
+                       int32_t total_blocks, int32_t least_blocks, const double* ycoef, hipStream_t s);
 
 // Density and velocity (double) of one sample; parity selects the AA layout.
 hipError_t launch_moments(int q, int precision, const void* pop, const DevSample* samples, int32_t sample,
@@ -118,10 +118,10 @@ hipError_t launch_adjoint_step(int q, int precision, const void* state, const vo
                                int32_t total_blocks, int32_t block, int32_t buffer_ok, int32_t exact_gamma,
                                hipStream_t s);
 hipError_t launch_init_adjoint(int q, int precision, const void* lam, const DevSample* samples, const Seg* segs,
-                               int32_t nseg, int32_t total_blocks, int32_t most_blocks, const double* ycoef,
+                               int32_t nseg, int32_t total_blocks, int32_t least_blocks, const double* ycoef,
                                double* partials, hipStream_t s);
 hipError_t launch_init_adjoint_finalize(const double* partials, const Seg* segs, int32_t nseg, int32_t total_blocks,
-                                        const DevSample* samples, const double* pmat, double* dJdY,
+                                        int32_t least_blocks, const DevSample* samples, const double* pmat, double* dJdY,
                                         hipStream_t s);
 hipError_t launch_extract(const double* records, int32_t m, int32_t field, double* out, hipStream_t s);
 

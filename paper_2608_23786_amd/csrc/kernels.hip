@@ -8,8 +8,6 @@
 namespace mclbm {
 namespace {
 
-constexpr int kMaxGridY = 65535;
-
 // Records from the block partials, in two stages where a sample has more than
 // kRecordChunk blocks: each block of the first adds up kRecordChunk rows in place,
 // into the first of them (which no other block touches), and the second stage
@@ -29,19 +27,16 @@ __device__ __forceinline__ void add_record_rows(const double* rows, int count, s
   block_record<256>(v, res);
 }
 
-__global__ void __launch_bounds__(256) record_chunk_kernel(double* partials, const Seg* segs, int nseg) {
-  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
-    const Seg sg = segs[k];
-    const int first = blockIdx.x * kRecordChunk, left = sg.nblocks - first;
-    if (sg.nblocks <= kRecordChunk || left <= 0) continue;
-    double* rows = partials + size_t(sg.first_block + first) * kRecord;
-    double res[kRecord];
-    add_record_rows(rows, left < kRecordChunk ? left : kRecordChunk, 1, res);
-    if (threadIdx.x == 0) {  // after the barrier of the reduction: every row is read
+__global__ void __launch_bounds__(256)
+    record_chunk_kernel(double* partials, const Seg* segs, int nseg, int total_blocks) {
+  const BlockChunk c = chunk_in_window(segs, nseg, total_blocks, kRecordChunk, blockIdx.x);
+  if (c.count == 0) return;
+  double* rows = partials + size_t(c.first) * kRecord;
+  double res[kRecord];
+  add_record_rows(rows, c.count, 1, res);
+  if (threadIdx.x == 0) {  // after the barrier of the reduction: every row is read
 #pragma unroll
-      for (int q = 0; q < kRecord; ++q) rows[q] = res[q];
-    }
-    __syncthreads();  // the reduction's LDS is free again
+    for (int q = 0; q < kRecord; ++q) rows[q] = res[q];
   }
 }
 
@@ -99,34 +94,26 @@ __global__ void __launch_bounds__(256)
     init_kernel(T* __restrict__ pop, const DevSample* __restrict__ samples, const Seg* __restrict__ segs, int nseg, int per,
                 const double* __restrict__ ycoef) {
   __shared__ double2 sc[kMaxN];
-  int table_n = 0;
-  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
-    const Seg sg = segs[k];
-    const int first = blockIdx.x * per, last = first + per < sg.nblocks ? first + per : sg.nblocks;
-    if (first >= last) continue;
-    const DevSample& sp = samples[sg.sample];
-    const int l = sp.log2n, n = 1 << l, msk = n - 1;
-    if (n != table_n) {
-      __syncthreads();
-      make_axis_table(sc, n);
-      __syncthreads();
-      table_n = n;
-    }
-    const double* yc = ycoef + size_t(sg.sample) * 24;
-    T* base = pop + sp.offset;
-    for (int b = first; b < last; ++b) {
-      const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
-      const int x = int(cell) & msk, y = int(cell >> l) & msk, z = int(cell >> (2 * l));
-      double u[3];
-      initial_velocity(sc[x], sc[(2 * x) & msk], sc[y], sc[(2 * y) & msk], sc[z], sc[(2 * z) & msk], sp.u0, sp.amp, yc, u);
-      const double usq15 = 1.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-      for_vel<QN>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        const double cu = double(cx(i)) * u[0] + double(cy(i)) * u[1] + double(cz(i)) * u[2];
-        const double gi = weight<QN>(i) * (3.0 * cu + 4.5 * cu * cu - usq15);
-        st(base + size_t(plane_of<QN>(i)) * sp.pstride, cell, T(gi));
-      });
-    }
+  const Seg sg = segs[find_segment(segs, nseg, int(blockIdx.x) * per)];
+  const int first = int(blockIdx.x) * per - sg.first_block, last = first + per;
+  const DevSample& sp = samples[sg.sample];
+  const int l = sp.log2n, n = 1 << l, msk = n - 1;
+  make_axis_table(sc, n);
+  __syncthreads();
+  const double* yc = ycoef + size_t(sg.sample) * 24;
+  T* base = pop + sp.offset;
+  for (int b = first; b < last; ++b) {
+    const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
+    const int x = int(cell) & msk, y = int(cell >> l) & msk, z = int(cell >> (2 * l));
+    double u[3];
+    initial_velocity(sc[x], sc[(2 * x) & msk], sc[y], sc[(2 * y) & msk], sc[z], sc[(2 * z) & msk], sp.u0, sp.amp, yc, u);
+    const double usq15 = 1.5 * (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
+    for_vel<QN>([&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      const double cu = double(cx(i)) * u[0] + double(cy(i)) * u[1] + double(cz(i)) * u[2];
+      const double gi = weight<QN>(i) * (3.0 * cu + 4.5 * cu * cu - usq15);
+      st(base + size_t(plane_of<QN>(i)) * sp.pstride, cell, T(gi));
+    });
   }
 }
 
@@ -527,85 +514,76 @@ __global__ void __launch_bounds__(256) init_adjoint_kernel(const T* __restrict__
   __shared__ double2 sc[kMaxN];
   __shared__ double sh[4][24];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int table_n = 0;
-  for (int k = blockIdx.y; k < nseg; k += gridDim.y) {
-    const Seg sg = segs[k];
-    const int first = blockIdx.x * per, last = first + per < sg.nblocks ? first + per : sg.nblocks;
-    if (first >= last) continue;
-    const DevSample& sp = samples[sg.sample];
-    const int l = sp.log2n, n = 1 << l, msk = n - 1;
-    if (n != table_n) {
-      __syncthreads();
-      make_axis_table(sc, n);
-      __syncthreads();
-      table_n = n;
-    }
-    const double* yc = ycoef + size_t(sg.sample) * 24;
-    const T* lb = lam + sp.offset;
-    double acc[24];
+  const Seg sg = segs[find_segment(segs, nseg, int(blockIdx.x) * per)];
+  const int first = int(blockIdx.x) * per - sg.first_block, last = first + per;
+  const DevSample& sp = samples[sg.sample];
+  const int l = sp.log2n, n = 1 << l, msk = n - 1;
+  make_axis_table(sc, n);
+  __syncthreads();
+  const double* yc = ycoef + size_t(sg.sample) * 24;
+  const T* lb = lam + sp.offset;
+  double acc[24];
 #pragma unroll
-    for (int p = 0; p < 24; ++p) acc[p] = 0.0;
-    const int phases = n > 256 ? n / 256 : 1;  // groups per row
-    for (int phase = 0; phase < phases; ++phase) {
-      double in[3][4];
+  for (int p = 0; p < 24; ++p) acc[p] = 0.0;
+  const int phases = n > 256 ? n / 256 : 1;  // groups per row
+  for (int phase = 0; phase < phases; ++phase) {
+    double in[3][4];
 #pragma unroll
-      for (int q = 0; q < 12; ++q) in[q >> 2][q & 3] = 0.0;
-      const int b0 = first + ((phase - first) & (phases - 1));
-      const int x = int(uint32_t(b0) * 256u + threadIdx.x) & msk;
-      const double2 x1 = sc[x], x2 = sc[(2 * x) & msk];
-      for (int b = b0; b < last; b += phases) {
-        const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
-        T g[Q];  // all loads in flight before the first is used
-        for_vel<QN>([&](auto ic) {
-          constexpr int i = decltype(ic)::value;
-          g[i] = ld(lb + size_t(plane_of<QN>(i)) * sp.pstride, cell);
-        });
-        __builtin_amdgcn_sched_barrier(0);
-        const int y = int(cell >> l) & msk, z = int(cell >> (2 * l));
-        const double2 y2 = sc[(2 * y) & msk], z2 = sc[(2 * z) & msk];
-        double u[3];
-        initial_velocity(x1, x2, sc[y], y2, sc[z], z2, sp.u0, sp.amp, yc, u);
-        // ub = sum_i li (3 c_i + 9 (c_i.u) c_i - 3 u), li = w_i lambda_i
-        double sum = 0.0, l1[3] = {0.0, 0.0, 0.0}, l2[3] = {0.0, 0.0, 0.0};
-        for_vel<QN>([&](auto ic) {
-          constexpr int i = decltype(ic)::value;
-          const double li = double(g[i]) * weight<QN>(i);
-          sum += li;
-          if constexpr (nonzeros(i) > 0) {
-            const double lcu = li * cdot<i>(u[0], u[1], u[2]);
-            if constexpr (cx(i) != 0) { l1[0] += cx(i) * li; l2[0] += cx(i) * lcu; }
-            if constexpr (cy(i) != 0) { l1[1] += cy(i) * li; l2[1] += cy(i) * lcu; }
-            if constexpr (cz(i) != 0) { l1[2] += cz(i) * li; l2[2] += cz(i) * lcu; }
-          }
-        });
-        const double jk[4] = {y2.x * z2.x, y2.x * z2.y, y2.y * z2.x, y2.y * z2.y};
-#pragma unroll
-        for (int al = 0; al < 3; ++al) {
-          const double ub = 3.0 * l1[al] + 9.0 * l2[al] - 3.0 * u[al] * sum;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) in[al][q] += ub * jk[q];
+    for (int q = 0; q < 12; ++q) in[q >> 2][q & 3] = 0.0;
+    const int b0 = first + ((phase - first) & (phases - 1));
+    const int x = int(uint32_t(b0) * 256u + threadIdx.x) & msk;
+    const double2 x1 = sc[x], x2 = sc[(2 * x) & msk];
+    for (int b = b0; b < last; b += phases) {
+      const uint32_t cell = uint32_t(b) * 256u + threadIdx.x;
+      T g[Q];  // all loads in flight before the first is used
+      for_vel<QN>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        g[i] = ld(lb + size_t(plane_of<QN>(i)) * sp.pstride, cell);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      const int y = int(cell >> l) & msk, z = int(cell >> (2 * l));
+      const double2 y2 = sc[(2 * y) & msk], z2 = sc[(2 * z) & msk];
+      double u[3];
+      initial_velocity(x1, x2, sc[y], y2, sc[z], z2, sp.u0, sp.amp, yc, u);
+      // ub = sum_i li (3 c_i + 9 (c_i.u) c_i - 3 u), li = w_i lambda_i
+      double sum = 0.0, l1[3] = {0.0, 0.0, 0.0}, l2[3] = {0.0, 0.0, 0.0};
+      for_vel<QN>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const double li = double(g[i]) * weight<QN>(i);
+        sum += li;
+        if constexpr (nonzeros(i) > 0) {
+          const double lcu = li * cdot<i>(u[0], u[1], u[2]);
+          if constexpr (cx(i) != 0) { l1[0] += cx(i) * li; l2[0] += cx(i) * lcu; }
+          if constexpr (cy(i) != 0) { l1[1] += cy(i) * li; l2[1] += cy(i) * lcu; }
+          if constexpr (cz(i) != 0) { l1[2] += cz(i) * li; l2[2] += cz(i) * lcu; }
         }
+      });
+      const double jk[4] = {y2.x * z2.x, y2.x * z2.y, y2.y * z2.x, y2.y * z2.y};
+#pragma unroll
+      for (int al = 0; al < 3; ++al) {
+        const double ub = 3.0 * l1[al] + 9.0 * l2[al] - 3.0 * u[al] * sum;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) in[al][q] += ub * jk[q];
       }
-#pragma unroll
-      for (int al = 0; al < 3; ++al)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc[8 * al + q] += x2.x * in[al][q];
-          acc[8 * al + 4 + q] += x2.y * in[al][q];
-        }
     }
-    const double scale = sp.amp * sp.u0 * 0.125;
 #pragma unroll
-    for (int p = 0; p < 24; ++p) {
-      const double v = wave_sum(acc[p]);
-      if (lane == 0) sh[wave][p] = scale * v;
-    }
-    __syncthreads();
-    if (threadIdx.x < 24) {
-      const int p = threadIdx.x;
-      partials[size_t(sg.first_block + first) * 24 + p] = ((sh[0][p] + sh[1][p]) + sh[2][p]) + sh[3][p];
-    }
-    __syncthreads();
+    for (int al = 0; al < 3; ++al)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        acc[8 * al + q] += x2.x * in[al][q];
+        acc[8 * al + 4 + q] += x2.y * in[al][q];
+      }
+  }
+  const double scale = sp.amp * sp.u0 * 0.125;
+#pragma unroll
+  for (int p = 0; p < 24; ++p) {
+    const double v = wave_sum(acc[p]);
+    if (lane == 0) sh[wave][p] = scale * v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 24) {
+    const int p = threadIdx.x;
+    partials[size_t(sg.first_block + first) * 24 + p] = ((sh[0][p] + sh[1][p]) + sh[2][p]) + sh[3][p];
   }
 }
 
@@ -767,11 +745,11 @@ hipError_t launch_step2(int q, int precision, const Step2Launch& L, hipStream_t 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nseg, int32_t most_blocks,
-                                  const DevSample* samples, double* out, hipStream_t s) {
+hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nseg, int32_t total_blocks,
+                                  int32_t most_blocks, const DevSample* samples, double* out, hipStream_t s) {
   if (most_blocks > kRecordChunk) {
-    const dim3 grid(unsigned((most_blocks + kRecordChunk - 1) / kRecordChunk), unsigned(std::min(nseg, kMaxGridY)));
-    hipLaunchKernelGGL(record_chunk_kernel, grid, dim3(256), 0, s, partials, segs, nseg);
+    const dim3 grid(unsigned((total_blocks + kRecordChunk - 1) / kRecordChunk));
+    hipLaunchKernelGGL(record_chunk_kernel, grid, dim3(256), 0, s, partials, segs, nseg, total_blocks);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -782,19 +760,21 @@ hipError_t launch_record_finalize(double* partials, const Seg* segs, int32_t nse
 namespace {
 // Groups of 256 nodes per block of the kernels of the initial data: enough blocks
 // to fill the card first, then up to 16 groups, which share a block's table of
-// sines and its reduction.
-int groups_per_block(int32_t total_blocks) { return std::max(1, std::min(16, total_blocks / 2048)); }
-dim3 group_grid(int32_t most_blocks, int per, int32_t nseg) {
-  return dim3(unsigned((most_blocks + per - 1) / per), unsigned(std::min(nseg, kMaxGridY)));
+// sines and its reduction; a power of two that divides every sample's groups, so
+// that a block's groups are of one sample.
+int groups_per_block(int32_t total_blocks, int32_t least_blocks) {
+  int per = 1;
+  while (2 * per <= std::min(16, std::min(least_blocks, total_blocks / 2048))) per *= 2;
+  return per;
 }
 }  // namespace
 
 hipError_t launch_init(int q, int precision, void* pop, const DevSample* samples, const Seg* segs, int32_t nseg,
-                       int32_t total_blocks, int32_t most_blocks, const double* ycoef, hipStream_t s) {
-  const int per = groups_per_block(total_blocks);
+                       int32_t total_blocks, int32_t least_blocks, const double* ycoef, hipStream_t s) {
+  const int per = groups_per_block(total_blocks, least_blocks);
   return dispatch(q, precision, [&](auto qc, auto tc) {
     using T = decltype(tc);
-    hipLaunchKernelGGL((init_kernel<decltype(qc)::value, T>), group_grid(most_blocks, per, nseg), dim3(256), 0, s,
+    hipLaunchKernelGGL((init_kernel<decltype(qc)::value, T>), dim3(total_blocks / per), dim3(256), 0, s,
                        static_cast<T*>(pop), samples, segs, nseg, per, ycoef);
     return hipGetLastError();
   });
@@ -946,22 +926,22 @@ hipError_t launch_adjoint_step(int q, int precision, const void* state, const vo
 }
 
 hipError_t launch_init_adjoint(int q, int precision, const void* lam, const DevSample* samples, const Seg* segs,
-                               int32_t nseg, int32_t total_blocks, int32_t most_blocks, const double* ycoef,
+                               int32_t nseg, int32_t total_blocks, int32_t least_blocks, const double* ycoef,
                                double* partials, hipStream_t s) {
-  const int per = groups_per_block(total_blocks);
+  const int per = groups_per_block(total_blocks, least_blocks);
   return dispatch(q, precision, [&](auto qc, auto tc) {
     using T = decltype(tc);
-    hipLaunchKernelGGL((init_adjoint_kernel<decltype(qc)::value, T>), group_grid(most_blocks, per, nseg), dim3(256), 0, s,
+    hipLaunchKernelGGL((init_adjoint_kernel<decltype(qc)::value, T>), dim3(total_blocks / per), dim3(256), 0, s,
                        static_cast<const T*>(lam), samples, segs, nseg, per, ycoef, partials);
     return hipGetLastError();
   });
 }
 
 hipError_t launch_init_adjoint_finalize(const double* partials, const Seg* segs, int32_t nseg, int32_t total_blocks,
-                                        const DevSample* samples, const double* pmat, double* dJdY,
+                                        int32_t least_blocks, const DevSample* samples, const double* pmat, double* dJdY,
                                         hipStream_t s) {
   hipLaunchKernelGGL(init_adjoint_finalize_kernel, dim3(nseg), dim3(24 * kInitParts), 0, s, partials, segs,
-                     groups_per_block(total_blocks), samples, pmat, dJdY);
+                     groups_per_block(total_blocks, least_blocks), samples, pmat, dJdY);
   return hipGetLastError();
 }
 

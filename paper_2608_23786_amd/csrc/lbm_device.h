@@ -1091,6 +1091,30 @@ __host__ __device__ __forceinline__ int find_segment(const Seg* segs, int nseg, 
   return lo;
 }
 
+// The rows of a launch's segments of more than `chunk` blocks in chunks, by windows
+// of `chunk` of the launch's blocks: the chunk that starts in window `window`
+// ({0, 0} where none does). Segments that long hold a power of two of chunks,
+// at least two, so at most one chunk starts in a window, and a segment that
+// starts in a window holds the window's last block.
+struct BlockChunk {
+  int32_t first, count;  // block within the launch
+};
+__host__ __device__ __forceinline__ BlockChunk chunk_in_window(const Seg* segs, int nseg, int total_blocks, int chunk,
+                                                               int window) {
+  const int w = window * chunk, e = w + chunk < total_blocks ? w + chunk - 1 : total_blocks - 1;
+  const Seg b = segs[find_segment(segs, nseg, e)];
+  if (b.nblocks > chunk) {
+    const int start = b.first_block + (e - b.first_block) / chunk * chunk;
+    return start >= w ? BlockChunk{start, chunk} : BlockChunk{0, 0};
+  }
+  const Seg a = segs[find_segment(segs, nseg, w)];
+  if (a.nblocks > chunk) {
+    const int start = a.first_block + (w - a.first_block + chunk - 1) / chunk * chunk;
+    if (start < a.first_block + a.nblocks) return {start, chunk};
+  }
+  return {0, 0};
+}
+
 // a value that is the same in every lane, in scalar registers
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) {
   return uint32_t(__builtin_amdgcn_readfirstlane(int(v)));
