@@ -33,7 +33,8 @@ struct StepArgs {
 // 64 x 64^3 616 / 601 / 580, 8 x 128^3 645 / 638 / 616, one 256^3 659 / 644 / 626,
 // 1000 x 32^3 1228 / 1215 / 1163; D3Q19 421 / 419 / 406, 444 / 443 / 428, 450 / 446 /
 // 431, 821 / 832 / 820. On either side of the lines the waves help more than they
-// cost: 8 x 64^3 75.9 free, 77.0 held (16 x 64^3 149.8, 148.4); 512^3 5858, 6016.
+// cost: 8 x 64^3 75.9 free, 77.0 held (16 x 64^3 149.8, 148.4); 512^3 5858, 6016; and
+// in record ticks, which wait for their sums (64 x 64^3 610 free, 675 held).
 constexpr int64_t kCapNodes = 1 << 22, kCapMost = 1 << 26;
 constexpr unsigned cap_lds(int block) { return unsigned(160 * 1024 / (3 * 256 / block)) - 4096; }
 
@@ -152,8 +153,8 @@ hipError_t launch_step_t(const StepLaunch& L, hipStream_t s) {
   a.vel = L.vel;
   const dim3 grid(L.total_blocks), blk(BLOCK);
   const int64_t nodes = int64_t(L.total_blocks) * BLOCK;
-  const bool cap = std::is_same<T, float>::value && BLOCK <= 256 && KIND != kReduceOnly && nodes >= kCapNodes &&
-                   nodes <= kCapMost;
+  const bool cap = std::is_same<T, float>::value && BLOCK <= 256 && (KIND == kStep || KIND == kPush) &&
+                   nodes >= kCapNodes && nodes <= kCapMost;
   const unsigned lds = cap ? cap_lds(BLOCK) : 0;
   auto launch = [&](auto args) {
     constexpr bool ARGS = decltype(args)::value;
