@@ -894,16 +894,19 @@ __global__ void __launch_bounds__(64 * kW1Columns)
 }
 
 // The same with one block per column for 1024 < m <= 4096, more values than a
-// wave's registers hold in a network of bounded code size: bitonic sort in LDS.
+// wave's registers hold in a network of bounded code size: bitonic sort in LDS
+// (whose comparisons would carry a NaN to any place; the column becomes NaN here too).
 __global__ void __launch_bounds__(256) w1_column_kernel(const double* a, const double* b, int m, int q3, int p2,
                                                         double* col) {
   __shared__ double sa[4096], sb[4096];
   const int c = blockIdx.x;  // column = comp * q3 + node
+  bool nan = false;
   for (int i = threadIdx.x; i < p2; i += 256) {
     sa[i] = i < m ? a[size_t(i) * 3 * q3 + c] : 1.0e308;
     sb[i] = i < m ? b[size_t(i) * 3 * q3 + c] : 1.0e308;
+    nan = nan || sa[i] != sa[i] || sb[i] != sb[i];
   }
-  __syncthreads();
+  nan = __syncthreads_or(nan);
   for (int k = 2; k <= p2; k <<= 1) {
     for (int j = k >> 1; j > 0; j >>= 1) {
       for (int i = threadIdx.x; i < p2; i += 256) {
@@ -935,7 +938,7 @@ __global__ void __launch_bounds__(256) w1_column_kernel(const double* a, const d
     if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
     __syncthreads();
   }
-  if (threadIdx.x == 0) col[c] = red[0] / m;
+  if (threadIdx.x == 0) col[c] = nan ? __builtin_nan("") : red[0] / m;
 }
 
 // out[c] = (1/q^3) sum over nodes of the column distances of component c.
