@@ -70,6 +70,13 @@ constexpr int y_lines(int n) { return n >= 512 ? 4 : (n == 32 ? 32 : (n >= 16 ? 
 // 256^3 with 4 / 8 / 16 lines 276 / 277 / 300, of twelve 128^3 198 / 189 / 223).
 constexpr int z_lines(int n) { return n == 128 || n == 256 ? 8 : y_lines(n); }
 
+// Threads per block of the passes that end in shell sums. Up to 64 the transforms
+// of a block take 16 to 128 threads, too few for its shell sums, which are as long
+// a chain of instructions: the block has 256, all of which take (line, shell)
+// pairs (us with the transforms' threads alone / with 256: z pass of four samples
+// of 32^3 19.7 / 9.0, of two of 64^3 16.2 / 10.2; last pass 8.8 / 5.2, 9.4 / 6.5).
+constexpr int sum_threads(int n, int transform_threads) { return n <= 64 ? 256 : transform_threads; }
+
 // Pairs of real lines per block of the folded inverse passes along y and x
 // (one complex transform per pair)
 constexpr int cos_pairs(int n) { return n >= 512 ? 4 : (n >= 128 ? 8 : 16); }
@@ -459,14 +466,15 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) fft_y_kernel(double2* 
 // so it writes one contiguous run. One LDS area serves all three, which
 // keeps a block at the transform's LDS.
 template <int N, int LINES>
-__global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const double2* h0, double* g0, double* sbins0,
+__global__ void __launch_bounds__(sum_threads(N, LINES * fft_threads(N))) z_psd_kernel(const double2* h0, double* g0, double* sbins0,
                                                                        size_t wstride) {
   constexpr int NH = N / 2 + 1, HALF = N / 2, LS = lds_half_line<N, LINES>(), E = fft_elems(N), TPL = fft_threads(N);
-  constexpr int THREADS = LINES * TPL;
+  constexpr int THREADS = sum_threads(N, LINES * TPL);
+  constexpr bool PAIRWISE = THREADS > LINES * TPL;  // a thread per (line, shell), beyond those of the transforms
   // Psi of every line (an odd number of doubles apart) lives in the transform's LDS
   // between the forward and the inverse transforms, then the folded lines
   constexpr int PS = N + 1, HP = HALF + 1;
-  constexpr int SH = LS > PS ? LS : PS;
+  constexpr int USED = PS + (PAIRWISE ? HP : 0), SH = LS > USED ? LS : USED;
   __shared__ double sh[LINES * SH];
   __shared__ double tot[(THREADS + 63) / 64], last[LINES];
   __shared__ double2 tw[N];
@@ -476,6 +484,7 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
   double* sbins = in_batch(sbins0, wstride);
   const int line0 = remap_block(blockIdx.x, gridDim.x, 1) * LINES;
   const int l = threadIdx.x % LINES, t = threadIdx.x / LINES;
+  const bool active = !PAIRWISE || t < TPL;
   double* const ln = sh + l * LS;
   const double2* d = in_batch(h0, wstride) + size_t(t) * field / N + line0 + l;   // lines are (y, kx), kx fastest
   make_twiddles<N>(tw);
@@ -484,13 +493,17 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
   for (int m = 0; m < E; ++m) ps[m] = 0.0;
   for (int c = 0; c < 3; ++c) {
     double2 x[E];
+    if (active) {
 #pragma unroll
-    for (int m = 0; m < E; ++m) x[m] = d[m * (TPL * field / N)];
+      for (int m = 0; m < E; ++m) x[m] = d[m * (TPL * field / N)];
+    }
     d += field;
     __syncthreads();  // the twiddles are there; the field before is read
-    fft_line<N, -1>(x, t, ln, tw);
+    fft_line<N, -1>(x, t, ln, tw, active);
+    if (active) {
 #pragma unroll
-    for (int m = 0; m < E; ++m) ps[m] += x[m].x * x[m].x + x[m].y * x[m].y;
+      for (int m = 0; m < E; ++m) ps[m] += x[m].x * x[m].x + x[m].y * x[m].y;
+    }
   }
   __syncthreads();  // Psi overwrites sh
   // Psi folded by |kz| with the weight |k|^2 of its mode, in two halves that are
@@ -498,11 +511,13 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
   // Nyquist value is its own partner, a half in either)
   const int myline = line0 + l, myx = myline % NH, myy = myline / NH;
   const double s_xy = double(myx) * myx + double(myy <= HALF ? myy : N - myy) * (myy <= HALF ? myy : N - myy);
+  if (active) {
 #pragma unroll
-  for (int m = 0; m < E; ++m) {
-    const int k = t + m * TPL, kf = k <= HALF ? k : N - k;
-    const double w = fma(double(kf), double(kf), s_xy) * ps[m];
-    psi[l * PS + k] = k == HALF ? 0.5 * w : w;
+    for (int m = 0; m < E; ++m) {
+      const int k = t + m * TPL, kf = k <= HALF ? k : N - k;
+      const double w = fma(double(kf), double(kf), s_xy) * ps[m];
+      psi[l * PS + k] = k == HALF ? 0.5 * w : w;
+    }
   }
   if (t == 0) psi[l * PS + N] = 0.0;
   double total = 0.0;
@@ -514,26 +529,40 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
   for (int o = LANES / 2; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
   if (threadIdx.x % LANES == 0) tot[threadIdx.x / LANES] = total;
   __syncthreads();
-  // the shell sums, a shell per thread: the block's lines added in order. The
-  // last shell, one too many for the threads at 128 and 256, takes a thread per line.
+  // the shell sums, the block's lines added in order
   const size_t blk = size_t(line0 / LINES);
-  for (int e = threadIdx.x; e < HALF + LINES; e += THREADS) {
-    const int r = e < HALF ? e : HALF, k0 = e < HALF ? 0 : e - HALF, k1 = e < HALF ? LINES : k0 + 1;
-    double sum = 0.0;
-    for (int k = k0; k < k1; ++k) {
-      const int line = line0 + k, y = line / NH, kx = line % NH;
-      const int ky = y <= HALF ? y : y - N;
-      const double* pl = psi + k * PS;
-      int a, b;
-      shell_range(HALF, kx * kx + ky * ky, r, a, b);
-      double part = 0.0;
-      for (int m = a; m <= b; ++m) part += pl[m] + pl[N - m];
-      sum += (kx == 0 || kx == HALF ? 0.5 : 1.0) * part;   // half of the mode's weight in |k|^2 / 2
-    }
-    if (e < HALF)
+  // of one line, times half of the mode's weight in |k|^2 / 2
+  auto line_sum = [&](int k, int r) {
+    const int line = line0 + k, y = line / NH, kx = line % NH;
+    const int ky = y <= HALF ? y : y - N;
+    const double* pl = psi + k * PS;
+    int a, b;
+    shell_range(HALF, kx * kx + ky * ky, r, a, b);
+    double part = 0.0;
+    for (int m = a; m <= b; ++m) part += pl[m] + pl[N - m];
+    return (kx == 0 || kx == HALF ? 0.5 : 1.0) * part;
+  };
+  if constexpr (PAIRWISE) {
+    double* const part = sh + LINES * PS;  // [LINES][HP]
+    for (int e = threadIdx.x; e < LINES * HP; e += THREADS) part[e] = line_sum(e / HP, e % HP);
+    __syncthreads();
+    for (int r = threadIdx.x; r <= HALF; r += THREADS) {
+      double sum = 0.0;
+      for (int k = 0; k < LINES; ++k) sum += part[k * HP + r];
       sbins[blk * (HALF + 2) + r] = sum;
-    else
-      last[k0] = sum;
+    }
+  } else {
+    // a shell per thread; the last shell, one too many for the threads at 128 and
+    // 256, takes a thread per line
+    for (int e = threadIdx.x; e < HALF + LINES; e += THREADS) {
+      const int r = e < HALF ? e : HALF, k0 = e < HALF ? 0 : e - HALF, k1 = e < HALF ? LINES : k0 + 1;
+      double sum = 0.0;
+      for (int k = k0; k < k1; ++k) sum += line_sum(k, r);
+      if (e < HALF)
+        sbins[blk * (HALF + 2) + r] = sum;
+      else
+        last[k0] = sum;
+    }
   }
   if (threadIdx.x == 0) {
     double sum = 0.0;
@@ -541,7 +570,7 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
     sbins[blk * (HALF + 2) + HALF + 1] = sum;
   }
   __syncthreads();  // Psi and the sums are read; the inverse overwrites sh
-  if (threadIdx.x == 0) {
+  if (!PAIRWISE && threadIdx.x == 0) {
     double sum = 0.0;
     for (int k = 0; k < LINES; ++k) sum += last[k];
     sbins[blk * (HALF + 2) + HALF] = sum;
@@ -549,14 +578,14 @@ __global__ void __launch_bounds__(LINES * fft_threads(N)) z_psd_kernel(const dou
   double2 x[E];
 #pragma unroll
   for (int m = 0; m < E; ++m) x[m] = make_double2(ps[m], 0.0);
-  fft_line<N, +1>(x, t, ln, tw);
+  fft_line<N, +1>(x, t, ln, tw, active);
   __syncthreads();  // the transform's reads are done; sh stages the output
   // outputs 0..N/2; mu is 2 except at 0 and N/2
   double* const stage = sh;
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     const int f = t + m * TPL;
-    if (f <= HALF) stage[l * HP + f] = fold_weight(f, HALF) * x[m].x;
+    if (active && f <= HALF) stage[l * HP + f] = fold_weight(f, HALF) * x[m].x;
   }
   __syncthreads();
   double* out = g + size_t(line0) * HP;
@@ -621,10 +650,10 @@ __global__ void __launch_bounds__(PAIRS * fft_threads(N)) cos_y_kernel(const dou
 // N^6 (the sum of Psi). Rows past (N/2 + 1)^2 transform zeros and add
 // nothing.
 template <int N, int PAIRS>
-__global__ void __launch_bounds__(PAIRS * fft_threads(N))
+__global__ void __launch_bounds__(sum_threads(N, PAIRS * fft_threads(N)))
     cos_x_kernel(const double* hin0, const double* r00, double* rbins0, size_t wstride) {
   constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), ROWS = 2 * PAIRS;
-  constexpr int E = fft_elems(N), TPL = fft_threads(N), THREADS = PAIRS * TPL;
+  constexpr int E = fft_elems(N), TPL = fft_threads(N), THREADS = sum_threads(N, PAIRS * TPL);
   // the transforms, then (as doubles) the rows' X values and their shell sums
   constexpr int SH = PAIRS * LS > ROWS * HP ? PAIRS * LS : ROWS * HP;
   __shared__ double2 sh[SH];
@@ -634,24 +663,27 @@ __global__ void __launch_bounds__(PAIRS * fft_threads(N))
   double* rbins = in_batch(rbins0, wstride);
   const int q0 = remap_block(blockIdx.x, gridDim.x, 1) * ROWS;
   const int p = threadIdx.x % PAIRS, t = threadIdx.x / PAIRS;
+  const bool active = t < TPL;
   const int qa = q0 + 2 * p, qb = qa + 1;
   const size_t ba = size_t(qa / HP) * J + qa % HP, bb = size_t(qb / HP) * J + qb % HP;
   double2 x[E];
+  if (active) {
 #pragma unroll
-  for (int m = 0; m < E; ++m) {
-    const int kx = t + m * TPL, kf = kx <= HALF ? kx : N - kx;  // the even extension
-    x[m] = make_double2(qa < J ? hin[ba + size_t(kf) * HP] : 0.0, qb < J ? hin[bb + size_t(kf) * HP] : 0.0);
+    for (int m = 0; m < E; ++m) {
+      const int kx = t + m * TPL, kf = kx <= HALF ? kx : N - kx;  // the even extension
+      x[m] = make_double2(qa < J ? hin[ba + size_t(kf) * HP] : 0.0, qb < J ? hin[bb + size_t(kf) * HP] : 0.0);
+    }
   }
   make_twiddles<N>(tw);
   __syncthreads();
-  fft_line<N, +1>(x, t, sh + p * LS, tw);
+  fft_line<N, +1>(x, t, sh + p * LS, tw, active);
   __syncthreads();  // the transform's reads are done; sh holds the rows next
   double* xr = reinterpret_cast<double*>(sh);  // [ROWS][HP]
   double* part = xr + ROWS * HP;                // [ROWS][HP]
 #pragma unroll
   for (int m = 0; m < E; ++m) {
     const int f = t + m * TPL;
-    if (f <= HALF) {
+    if (active && f <= HALF) {
       xr[(2 * p) * HP + f] = fold_weight(f, HALF) * x[m].x;
       xr[(2 * p + 1) * HP + f] = fold_weight(f, HALF) * x[m].y;
     }
@@ -1128,7 +1160,7 @@ hipError_t observables_t(const T* pop, const double* u, const DevSample* samples
                      sample0, parity, w.h, ws);
   constexpr int TPL = fft_threads(N);
   hipLaunchKernelGGL((fft_y_kernel<N, LY>), dim3(lines / LY, 3, z), dim3(LY * TPL), 0, s, w.h, ws);
-  hipLaunchKernelGGL((z_psd_kernel<N, LZ>), dim3(lines / LZ, 1, z), dim3(LZ * TPL), 0, s, w.h, w.g, w.sbins, ws);
+  hipLaunchKernelGGL((z_psd_kernel<N, LZ>), dim3(lines / LZ, 1, z), dim3(sum_threads(N, LZ * TPL)), 0, s, w.h, w.g, w.sbins, ws);
   hipLaunchKernelGGL(shell_partial_kernel, dim3(lchunks, 1, z), dim3(256), 0, s, w.sbins, srows, W, w.psum, ws);
   hipLaunchKernelGGL(shell_count_kernel, dim3(NH), dim3(256), 0, s, N, w.cnt);
   hipLaunchKernelGGL(shell_final_kernel, dim3(W, 1, z), dim3(256), 0, s, w.psum, w.cnt, lchunks, W, N, 0, ek, w.r0,
@@ -1136,7 +1168,7 @@ hipError_t observables_t(const T* pop, const double* u, const DevSample* samples
   if (s2) {
     double* hr = reinterpret_cast<double*>(w.h);
     hipLaunchKernelGGL((cos_y_kernel<N, PC>), dim3(rrows, 1, z), dim3(PC * TPL), 0, s, w.g, hr, ws);
-    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(PC * TPL), 0, s, hr, w.r0, w.rbins, ws);
+    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(sum_threads(N, PC * TPL)), 0, s, hr, w.r0, w.rbins, ws);
     hipLaunchKernelGGL(shell_partial_kernel, dim3(rchunks, 1, z), dim3(256), 0, s, w.rbins, rrows, W, w.psum, ws);
     hipLaunchKernelGGL(shell_final_kernel, dim3(W, 1, z), dim3(256), 0, s, w.psum, w.cnt, rchunks, W, N, 1, s2,
                        nullptr, ws);
