@@ -28,24 +28,26 @@ BYTES_PER_LUP = {("f32s", 27): 216, ("f64", 27): 432, ("f32s", 19): 152, ("f64",
 # is valid only for the exact sources it was taken with)
 STEP_SOURCES = ["lattice.h", "lbm_device.h", "step_kernel.h", "step_d3q27_f32.hip", "step_d3q27_f64.hip",
                 "step_d3q19_f32.hip", "step_d3q19_f64.hip"]
+# and those of the kernel that takes two steps per pass
+STEP2_SOURCES = STEP_SOURCES + ["step2_kernel.h"]
 
 
-def step_source_hash():
+def step_source_hash(sources=STEP_SOURCES):
     import hashlib
     h = hashlib.sha256()
-    for name in STEP_SOURCES:
+    for name in sources:
         h.update(open(os.path.join(ROOT, "paper_2608_23786_amd", "csrc", name), "rb").read())
     return h.hexdigest()
 
 
-def counter_traffic(workload):
-    """HBM bytes per collide-and-stream launch from the committed counter
-    summary, or None when the kernel source changed since it was taken."""
-    path = os.path.join(ROOT, "profiles", f"kbc_step_{workload}.traffic.txt")
+def counter_traffic(workload, kernel="kbc_step", sources=STEP_SOURCES):
+    """HBM bytes per launch of a kernel from the committed counter summary,
+    or None when its sources changed since it was taken."""
+    path = os.path.join(ROOT, "profiles", f"{kernel}_{workload}.traffic.txt")
     if not os.path.exists(path):
         return None
     vals = dict(line.strip().split("=", 1) for line in open(path) if "=" in line and not line.startswith("#"))
-    if step_source_hash() != vals.get("kernel_source_sha256"):
+    if step_source_hash(sources) != vals.get("kernel_source_sha256"):
         return None
     return int(vals["traffic_bytes_per_launch"])
 
@@ -111,6 +113,23 @@ def kernel_roofline(ens, wl, torch, ticks):
     bytes_per_launch = BYTES_PER_LUP[wl.precision, wl.lattice] * lups / launches
     achieved = bytes_per_launch / (avg_ms / 1e3) / 1e9
     return avg_ms, launches, bytes_per_launch, achieved
+
+
+def pass_roofline(ens, wl, torch, passes=20):
+    """The same of the kernel that the ticks between records run in, two steps
+    per pass over memory, from events around `passes` of them; None where the
+    ensemble takes single steps (several groups, too small, no buffer)."""
+    if len(wl.groups) != 1 or not ens.two_step(True):
+        return None
+    odd = int(ens.samples[0].n > 64)       # the passes' parity
+    ens.step((ens.steps(0) + odd) % 2)
+    sec, lups = timed_ticks(ens, torch, 2 * passes, 0)
+    bytes_per_pass = BYTES_PER_LUP[wl.precision, wl.lattice] * lups / (2 * passes)
+    achieved = bytes_per_pass / (sec / passes) / 1e9
+    return {"kernel": "kbc_step2_kernel", "steps_per_pass": 2, "avg_pass_ms": round(sec / passes * 1e3, 5),
+            "passes_timed": passes, "algorithmic_bytes_per_pass": int(round(bytes_per_pass)),
+            "traffic": counter_traffic(wl.name, "kbc_step2", STEP2_SOURCES), "achieved": round(achieved, 1),
+            "frac": round(achieved / HBM_PEAK_GBS, 4)}
 
 
 def launch_sweep(ens, wl, torch, ticks=20):
@@ -781,6 +800,8 @@ def main():
     avg_ms, launches, bpl, achieved = kernel_roofline(ens, wl, torch, args.roofline_ticks)
     print(f"[bench] collide-stream: {launches} launches, {avg_ms:.4f} ms avg, {achieved:.0f} GB/s algorithmic",
           file=sys.stderr, flush=True)
+    passes = pass_roofline(ens, wl, torch)
+    print(f"[bench] two-step passes: {passes}", file=sys.stderr, flush=True)
     f64 = f64_batch = None
     if not args.skip_fp64:
         f64 = {"32^3 TGV Re 100 MLUPS": round(fp64_single(mc, torch, 32, 0.05, 100.0), 1),
@@ -829,7 +850,10 @@ def main():
                      "traffic_unit": "bytes per launch", "algorithmic_bytes_per_launch": int(round(bpl)),
                      "kernel": "kbc_step_kernel", "bytes_per_lup": BYTES_PER_LUP[wl.precision, wl.lattice],
                      "avg_launch_ms": round(avg_ms, 5), "launches_timed": launches,
-                     "measured_copy_GBps": round(b_meas, 1), "frac_of_measured_copy": round(achieved / b_meas, 4)},
+                     "measured_copy_GBps": round(b_meas, 1), "frac_of_measured_copy": round(achieved / b_meas, 4),
+                     # what the ticks between records run in, and most of `value` with it; the launch shape in
+                     # `config` and the figures above are those of single steps
+                     "two_step_passes": passes},
         "fp64_single_sample": f64,
         **({"fp64_batched_64x64": f64_batch} if f64_batch else {}),
         **({"launch_sweep": sweep} if sweep else {}),

@@ -536,7 +536,8 @@ size_t state_bytes_of(const mclbm_ctx* c, int s) {
 // Samples per trip through scratch. Up to 64^3 as many as fit in 2 GiB (more
 // planes per team: fewer rim planes); longer lattices one at a time, whose
 // state is then still in the last-level cache for the way back at 128^3
-// (8 x 128^3: 899 us per two steps one by one, 1050 together) and whose scratch
+// (8 x 128^3, with a cheaper collision: 899 us per two steps one by one, 1050
+// together) and whose scratch
 // stays small.
 int run_chunk(const mclbm_ctx* c, const mclbm_ctx::Run& r) {
   if (c->desc[r.first].n > 64) return 1;

@@ -704,8 +704,8 @@ __device__ __forceinline__ CellResult<float> kbc_collide_each(float (&g)[Q], con
 // reciprocals instead of 27 and half the sums: D3Q27 in double takes 580 vector
 // instructions against 1130 velocity by velocity. (In float with the closed form
 // it would take 490 against 605, but round otherwise than the results have always
-// been; the passes of two steps, which are bound by arithmetic, took 3 to 4 % less
-// with it.)
+// been; the passes of two steps, which are bound by arithmetic, took 794 us with it
+// instead of 842 at 64 x 64^3, 887 instead of 1077 at 8 x 128^3.)
 // In float 6 w is split into head and tail for dn: with the rounded weights
 // alone sum_i 3 w_i c_i c_i = (1 + 7.5e-9) I, a systematic momentum gain in
 // every collision that accumulates over thousands of steps. The shear

@@ -10,10 +10,16 @@
 // place and the stores stream. After an odd number slot -i holds population i
 // after its collision: the loads stream (population i of node x from x - c_i) and
 // the stores are to the node's own place. Rows that lie whole in a tile stay in
-// whole lines either way and take the even layout (64 x 64^3: 794 us a pass
-// against 839); 64-node tiles of longer rows take the odd one, since stores off
-// their lines by one node write them in parts (256^3: 1.12 x the bytes, 1028 us
-// against 891; 8 x 128^3: 1050 against 887).
+// whole lines either way and take the even layout; 64-node tiles of longer rows
+// take the odd one, since stores off their lines by one node write them in parts
+// (1.12 x the bytes at 256^3). us a pass in the even / odd layout, taken with a
+// cheaper collision: 64 x 64^3 794 / 839, one 256^3 1028 / 891, 8 x 128^3 1050 / 887.
+//
+// us a pass / two single steps, FP32: 64 x 64^3 842 / 1162, 512 x 32^3 777 / 1180,
+// 8 x 128^3 1077 / 1240, one 256^3 961 / 1252, one 512^3 8078 / 11720; 64 x 64^3 of
+// D3Q19 598 / 811; FP64 64 x 64^3 1617 / 2386. Bound by arithmetic in FP32 (two
+// collisions of 700 issue slots and the rim's share per node), by what it reads
+// and writes, rims included, in FP64.
 //
 // A block owns a tile of nodes in the x-y plane and marches along z. Per plane
 // it loads the 27 populations of its nodes, takes the first collision, and

@@ -70,10 +70,10 @@ class Ensemble:
             nbytes = 256
         self.stream = stream if stream is not None else torch.cuda.Stream(device=self.device)
         self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
-        # the allocator may hand out memory that work queued on the caller's stream still uses:
-        # the library writes it on its own stream, and on the null stream while it sets up
+        # the allocator may hand out memory that work queued on the caller's stream still uses: the
+        # library writes it on its own stream, and on the null stream while it sets up (it drains
+        # its stream when it is destroyed, before the memory goes back)
         torch.cuda.current_stream(self.device).synchronize()
-        self._consume(self.workspace)
         base = self.workspace.data_ptr()
         self._ws_ptr = (base + 255) // 256 * 256
         self._ctx = ctypes.c_void_p()
