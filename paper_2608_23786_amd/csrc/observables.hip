@@ -70,12 +70,15 @@ constexpr int y_lines(int n) { return n >= 512 ? 4 : (n == 32 ? 32 : (n >= 16 ? 
 // 256^3 with 4 / 8 / 16 lines 276 / 277 / 300, of twelve 128^3 198 / 189 / 223).
 constexpr int z_lines(int n) { return n == 128 || n == 256 ? 8 : y_lines(n); }
 
-// Threads per block of the passes that end in shell sums. Up to 64 the transforms
-// of a block take 16 to 128 threads, too few for its shell sums, which are as long
-// a chain of instructions: the block has 256, all of which take (line, shell)
-// pairs (us with the transforms' threads alone / with 256: z pass of four samples
-// of 32^3 19.7 / 9.0, of two of 64^3 16.2 / 10.2; last pass 8.8 / 5.2, 9.4 / 6.5).
+// Threads per block of the passes that end in shell sums. The transforms of a block
+// take 16 to 128 threads, too few for its shell sums, which are as long a chain of
+// instructions: the block has 256, all of which take (line, shell) pairs, in the z
+// pass up to 64 (from 128 on the pairs' LDS would cost it blocks) and in the last
+// pass up to 256 (us with the transforms' threads alone / with 256: z pass of four
+// samples of 32^3 19.7 / 9.0, of two of 64^3 16.2 / 10.2; last pass 8.8 / 5.2, 9.4 /
+// 6.5, of twelve 128^3 38.0 / 30.5, of two 256^3 55.3 / 38.9).
 constexpr int sum_threads(int n, int transform_threads) { return n <= 64 ? 256 : transform_threads; }
+constexpr int last_threads(int n, int transform_threads) { return n <= 256 ? 256 : transform_threads; }
 
 // Pairs of real lines per block of the folded inverse passes along y and x
 // (one complex transform per pair)
@@ -650,10 +653,10 @@ __global__ void __launch_bounds__(PAIRS * fft_threads(N)) cos_y_kernel(const dou
 // N^6 (the sum of Psi). Rows past (N/2 + 1)^2 transform zeros and add
 // nothing.
 template <int N, int PAIRS>
-__global__ void __launch_bounds__(sum_threads(N, PAIRS * fft_threads(N)))
+__global__ void __launch_bounds__(last_threads(N, PAIRS * fft_threads(N)))
     cos_x_kernel(const double* hin0, const double* r00, double* rbins0, size_t wstride) {
   constexpr int HALF = N / 2, HP = HALF + 1, J = HP * HP, LS = lds_line<N>(), ROWS = 2 * PAIRS;
-  constexpr int E = fft_elems(N), TPL = fft_threads(N), THREADS = sum_threads(N, PAIRS * TPL);
+  constexpr int E = fft_elems(N), TPL = fft_threads(N), THREADS = last_threads(N, PAIRS * TPL);
   // the transforms, then (as doubles) the rows' X values and their shell sums
   constexpr int SH = PAIRS * LS > ROWS * HP ? PAIRS * LS : ROWS * HP;
   __shared__ double2 sh[SH];
@@ -1168,7 +1171,7 @@ hipError_t observables_t(const T* pop, const double* u, const DevSample* samples
   if (s2) {
     double* hr = reinterpret_cast<double*>(w.h);
     hipLaunchKernelGGL((cos_y_kernel<N, PC>), dim3(rrows, 1, z), dim3(PC * TPL), 0, s, w.g, hr, ws);
-    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(sum_threads(N, PC * TPL)), 0, s, hr, w.r0, w.rbins, ws);
+    hipLaunchKernelGGL((cos_x_kernel<N, PC>), dim3(rrows, 1, z), dim3(last_threads(N, PC * TPL)), 0, s, hr, w.r0, w.rbins, ws);
     hipLaunchKernelGGL(shell_partial_kernel, dim3(rchunks, 1, z), dim3(256), 0, s, w.rbins, rrows, W, w.psum, ws);
     hipLaunchKernelGGL(shell_final_kernel, dim3(W, 1, z), dim3(256), 0, s, w.psum, w.cnt, rchunks, W, N, 1, s2,
                        nullptr, ws);
