@@ -448,8 +448,10 @@ mclbm_status mclbm_dissipation_spectra(mclbm_ctx* ctx, int32_t first, int32_t co
  * MCLBM_ERR_ARG for any other mode. */
 mclbm_status mclbm_set_stabiliser(mclbm_ctx* ctx, int32_t mode);
 
-/* Launch shape of the collide-and-stream kernel, one for the whole ensemble
- * launch: threads (= lattice nodes) per block, 128, 256, 512 or 1024 (1024:
+/* Launch shape of the single-step collide-and-stream kernel (passes of two
+ * steps have their own), one for a whole launch; until it is set or tuned,
+ * launches of fewer than 2^18 nodes take 128 threads per block, others 256.
+ * Threads (= lattice nodes) per block, 128, 256, 512 or 1024 (1024:
  * FP32 only), not above any sample's n^3; xcd_remap = 1 renumbers blocks so
  * that each of the 8 XCDs works on one contiguous range of nodes;
  * buffer_addressing = 1 addresses the population planes through one buffer
@@ -462,7 +464,7 @@ mclbm_status mclbm_set_launch(mclbm_ctx* ctx, int32_t block_threads, int32_t xcd
 mclbm_status mclbm_get_launch(const mclbm_ctx* ctx, int32_t* block_threads, int32_t* xcd_remap,
                               int32_t* buffer_addressing, int32_t* nontemporal);
 
-/* Time every launch shape on the current state (`reps` periods of
+/* Time every launch shape on the current state in single steps (`reps` periods of
  * 2 * max stride ticks each, after one warm-up period), time the three
  * fastest twice more, keep the one with the best time,
  * and restore the state from a checkpoint written to scratch_dev
@@ -474,7 +476,9 @@ mclbm_status mclbm_autotune(mclbm_ctx* ctx, int32_t reps, void* scratch_dev, siz
 
 /* Capture the tick loop into HIP graphs (1, the default) or launch kernel by
  * kernel (0). Graphs are used only on a non-NULL stream, for runs of at
- * least one graph length (a whole number of activity/parity periods). */
+ * least one graph length (a whole number of activity/parity periods) of
+ * single steps; passes of two steps are launched directly, and the samples
+ * beside them are replayed in graphs of their own. */
 mclbm_status mclbm_use_graphs(mclbm_ctx* ctx, int32_t enable);
 
 /* Current tick counter and the number of steps sample s has taken. */
